@@ -191,17 +191,22 @@ __device__ __forceinline__ float mul_rd(float c, float x) {
     return __builtin_bit_cast(float, __builtin_fmaf(c, x, -u) < 0.f ? down : ub);
 }
 
-// E8M0 byte of a P~ block from the bits of its maximum M (0 <= M <= 1 + 2^-20):
-// e + 127 = E - 2 under the OCP floor rule and E - 2 + [fraction > 0x680000]
-// under UOS (as scale_exponent_f32), where adding 0x17FFFF carries into the
-// exponent field exactly when the 23-bit fraction exceeds 0x680000; clamped
-// at byte 0 (e >= -127).  A block whose maximum underflowed to 0 holds only
-// zeros, so its codes are all zero and its scale affects nothing: it gets
-// byte 0 here rather than the 127 of an all-zero input block.
+// The E8M0 exponent of a P~ block from the bits of its maximum M (0 <= M <=
+// 1 + 2^-20), in the exponent field of the result (whose lower 23 bits are
+// arbitrary): e + 127 = E - 2 under the OCP floor rule and
+// E - 2 + [fraction > 0x680000] under UOS (as scale_exponent_f32), where adding
+// 0x17FFFF carries into the exponent field exactly when the 23-bit fraction
+// exceeds 0x680000; clamped at byte 0 (e >= -127).  The conversion reads only
+// the exponent field of its scale operand (compared over every exponent and
+// random fractions on the hardware), so these bits serve it as they are and
+// the scale byte of the products is one shift away.  A block whose maximum
+// underflowed to 0 holds only zeros, so its codes are all zero and its scale
+// affects nothing: it gets byte 0 here rather than the 127 of an all-zero
+// input block.
 template <int kRule>
-__device__ __forceinline__ uint32_t p_scale_byte(uint32_t mbits) {
-    const int E = (int)((mbits + (kRule == kRuleUos ? 0x17FFFFu : 0u)) >> 23);
-    return (uint32_t)max(E - 2, 0);
+__device__ __forceinline__ uint32_t p_scale_bits(uint32_t mbits) {
+    const int x = (int)mbits + (kRule == kRuleUos ? 0x17FFFF : 0) - (2 << 23);
+    return (uint32_t)max(x, 0);
 }
 
 // LDS reads are ordinary loads from __shared__ arrays.  A lane reads its
@@ -473,9 +478,9 @@ __device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo
 #pragma unroll
     for (int c = 0; c < 2; c++) {
         const float mb = __builtin_amdgcn_exp2f(__builtin_fmaf(bmax[c], cl, -m_new));
-        const uint32_t sbyte = p_scale_byte<kRule>(__builtin_bit_cast(uint32_t, mb));
-        const float sf = e8m0_as_f32(sbyte);
-        const int psc = (int)sbyte;
+        const uint32_t sbits = p_scale_bits<kRule>(__builtin_bit_cast(uint32_t, mb));
+        const float sf = __builtin_bit_cast(float, sbits);
+        const int psc = (int)(sbits >> 23);
         uint32_t w[4];
 #pragma unroll
         for (int n = 0; n < 32; n += 2) {
@@ -706,7 +711,7 @@ template <int kRule>
 __device__ __forceinline__ uint32_t block_scale(float bmax, float m_new) {
     const float cl = 0.12751743082459868f;
     const float mb = __builtin_amdgcn_exp2f(__builtin_fmaf(bmax, cl, -m_new));
-    return p_scale_byte<kRule>(__builtin_bit_cast(uint32_t, mb));
+    return p_scale_bits<kRule>(__builtin_bit_cast(uint32_t, mb));
 }
 
 // State a wave carries from one KV tile to the next.
@@ -714,7 +719,7 @@ struct PipeState {
     v16f S[2][2];  // scores of the current tile
     v16f O[4];
     RowSum rs;
-    float m;
+    float m, smax;  // RD(c * smax), and the largest score so far
     v8i P1;        // P^ of the previous tile's chunk 1 (its products are deferred)
     int psc1;
     uint2 vsb1;    // V^ scales of the previous tile
@@ -756,9 +761,18 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
 #pragma unroll
     for (int c = 0; c < 2; c++) bmax[c] = block_max32(ps.S[c][0], ps.S[c][1]);
     const float rmax = max_with_other_half(max2f(bmax[0], bmax[1]));
-    const float m_new = max2f(ps.m, mul_rd(cl, rmax));
-    const float alpha = __builtin_amdgcn_exp2f(ps.m - m_new);  // 0 on the first tile
-    ps.m = m_new;
+    // the running maximum moves only where a row's score maximum rises (RD is
+    // monotone): on most tiles of a long sequence no row of the wave does, and
+    // its rounding and alpha are skipped
+    const bool rose = __any(rmax > ps.smax);
+    float alpha = 1.f;
+    if (rose) {
+        ps.smax = max2f(ps.smax, rmax);
+        const float m = mul_rd(cl, ps.smax);
+        alpha = __builtin_amdgcn_exp2f(ps.m - m);  // 0 on the first tile
+        ps.m = m;
+    }
+    const float m_new = ps.m;
 
     // ---- B: tile j+1 landed everywhere, and every wave has read tile j-1's
     // stage for the last time, so it takes tile j+2
@@ -785,7 +799,7 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
     float lsum = 0.f;
     uint32_t w0[4], w1[4];
     const uint32_t sb0 = block_scale<kRule>(bmax[0], m_new);
-    const float sf0 = e8m0_as_f32(sb0);
+    const float sf0 = __builtin_bit_cast(float, sb0);
     softmax_half<kRule, kPnq, 0>(ps.S[0][0], m_new, sf0, w0, lsum);
     ps.S[0][0] = score_pair<0, 0>(kn, qo, ksb);
     pin_here(ps.S[0][0][0], w0[0], w0[1], lsum, ps.O[0][0], ps.O[1][0], ps.O[2][0], ps.O[3][0], ps.rs.L[0], ksb,
@@ -793,7 +807,7 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
              kn.hi[1][1], vc0.v[0], vc0.v[1], vc0.v[2], vc0.v[3]);
 
     // the rescale of O~ and l by alpha follows the products above
-    if (__any(alpha != 1.f)) {
+    if (rose) {
 #pragma unroll
         for (int n = 0; n < 4; n++)
 #pragma unroll
@@ -811,9 +825,9 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
     softmax_half<kRule, kPnq, 1>(ps.S[0][1], m_new, sf0, w0, lsum);
     ps.S[0][1] = score_pair<0, 1>(kn, qo, ksb);
     const v8i P0 = fp4_operand(make_uint4(w0[0], w0[1], w0[2], w0[3]));
-    pv_chunk<kPnq, 0>(vc0, P0, (int)sb0, vsb, sel, ps.rs, ps.O);
+    pv_chunk<kPnq, 0>(vc0, P0, (int)(sb0 >> 23), vsb, sel, ps.rs, ps.O);
     const uint32_t sb1 = block_scale<kRule>(bmax[1], m_new);
-    const float sf1 = e8m0_as_f32(sb1);
+    const float sf1 = __builtin_bit_cast(float, sb1);
     softmax_half<kRule, kPnq, 0>(ps.S[1][0], m_new, sf1, w1, lsum);
     ps.S[1][0] = score_pair<1, 0>(kn, qo, ksb);
     pin_here(ps.S[1][0][0], w1[0], w1[1]);
@@ -822,7 +836,7 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
     pin_here(ps.S[0][0][0], ps.S[0][1][0], ps.S[1][0][0], ps.S[1][1][0], ps.O[0][0], ps.O[1][0], ps.O[2][0],
              ps.O[3][0]);
     ps.P1 = fp4_operand(make_uint4(w1[0], w1[1], w1[2], w1[3]));
-    ps.psc1 = (int)sb1;
+    ps.psc1 = (int)(sb1 >> 23);
     ps.vsb1 = vsb;
     if (!kPnq) ps.rs.l = alpha * ps.rs.l + lsum;
 }
@@ -863,7 +877,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
     const LaneOff lo = lane_off(q, h, lane);
 
     PipeState ps;
-    ps.m = -__builtin_inff();
+    ps.m = ps.smax = -__builtin_inff();
     ps.rs.l = 0.f;
     ps.rs.L = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
