@@ -320,32 +320,27 @@ int check_attention_shape(int64_t B, int64_t H, int64_t Nq, int64_t Nkv) {
     return MXATTN_OK;
 }
 
-// Rearranges the K^/V^ scales into sc (mxattn::tile_scales_bytes(B*H, Nkv)
-// bytes of workspace), then runs the fused attention kernel: on Q^ = (qc, qs),
-// or, when qraw is not null, on the bf16 Q that the kernel quantizes itself
-// (qc and qs are then unused).
+// The fused attention kernel: on Q^ = (qc, qs), or, when qraw is not null, on
+// the bf16 Q that the kernel quantizes itself (qc and qs are then unused); sc
+// holds the K^/V^ scales in operand order.  v_tiled: V^ codes stored tile by
+// tile (launch_prepare_operands) instead of in channel rows.
 static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs, const uint8_t* kc,
-                         const uint8_t* ks, const uint8_t* vc, const uint8_t* vs, uint8_t* sc,
-                         void* out, int64_t B, int64_t H, int64_t Nq, int64_t Nkv, int mode,
-                         hipStream_t s) {
-    hipError_t e = mxattn::launch_tile_scales(ks, vs, sc, B * H, Nkv, s);
-    if (e != hipSuccess) {
-        set_error("scale layout launch", e);
-        return MXATTN_ERR_HIP;
-    }
+                         const uint8_t* vc, bool v_tiled, const uint8_t* sc, void* out, int64_t B, int64_t H,
+                         int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
     mxattn::AttnArgs a;
     a.qc = qc;
     a.qs = qs;
     a.qraw = static_cast<const uint16_t*>(qraw);
     a.kc = kc;
-    a.ks = ks;
     a.vc = vc;
-    a.vs = vs;
+    const int ntiles = (int)((Nkv + mxattn::kKvTile - 1) / mxattn::kKvTile);
+    a.vrow = v_tiled ? 64 : (int)((Nkv + 31) / 32) * 16;
+    a.vtile = v_tiled ? 8192 : 64;
+    a.vhead = v_tiled ? ntiles * 8192 : 128 * a.vrow;
     a.sc = sc;
     a.out = static_cast<uint16_t*>(out);
     a.N = (int)Nkv;
     a.Nq = (int)Nq;
-    a.nb = (int)((Nkv + 31) / 32);
     a.qtiles = (int)((Nq + mxattn::kQueryTile - 1) / mxattn::kQueryTile);
     // one query tile per workgroup; with K^/V^ resident in LDS, chunks of at
     // most 16 query tiles, as many as fill whole rounds of the 512 workgroups
@@ -362,12 +357,25 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
     const int64_t total = B * H * a.nchunks;
     a.total_tiles = (int)total;
     a.per_xcd = (int)((total + 7) / 8);
-    e = mxattn::launch_attention(a, kernel_mode(mode), s);
+    hipError_t e = mxattn::launch_attention(a, kernel_mode(mode), s);
     if (e != hipSuccess) {
         set_error("attention launch", e);
         return MXATTN_ERR_HIP;
     }
     return MXATTN_OK;
+}
+
+// The same on operands in the public layouts: rearranges the K^/V^ scales into
+// sc (mxattn::tile_scales_bytes(B*H, Nkv) bytes of workspace) first.
+static int launch_attend_public(const uint8_t* qc, const uint8_t* qs, const uint8_t* kc, const uint8_t* ks,
+                                const uint8_t* vc, const uint8_t* vs, uint8_t* sc, void* out, int64_t B,
+                                int64_t H, int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
+    hipError_t e = mxattn::launch_tile_scales(ks, vs, sc, B * H, Nkv, s);
+    if (e != hipSuccess) {
+        set_error("scale layout launch", e);
+        return MXATTN_ERR_HIP;
+    }
+    return launch_attend(nullptr, qc, qs, kc, vc, false, sc, out, B, H, Nq, Nkv, mode, s);
 }
 
 // Whether `out` ([B, H, Nq, d] bf16) shares memory with any quantized operand.
@@ -416,8 +424,8 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
         set_error("workspace allocation", e);
         return MXATTN_ERR_OOM;
     }
-    int st = launch_attend(nullptr, q_codes, q_scales, k_codes, k_scales, v_codes, v_scales,
-                           static_cast<uint8_t*>(ws), out, B, H, Nq, Nkv, mode, s);
+    int st = launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales,
+                                  static_cast<uint8_t*>(ws), out, B, H, Nq, Nkv, mode, s);
     e = hipFreeAsync(ws, s);
     if (st == MXATTN_OK && e != hipSuccess) {
         set_error("hipFreeAsync", e);
@@ -493,8 +501,8 @@ int mxattn_cross_attend_noalloc(const uint8_t* q_codes, const uint8_t* q_scales,
     }
     void* sc = nullptr;
     if (int st = scratch_address(&sc)) return st;
-    return launch_attend(nullptr, q_codes, q_scales, k_codes, k_scales, v_codes, v_scales, static_cast<uint8_t*>(sc),
-                         out, B, H, Nq, Nkv, mode, reinterpret_cast<hipStream_t>(stream));
+    return launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales, static_cast<uint8_t*>(sc),
+                                out, B, H, Nq, Nkv, mode, reinterpret_cast<hipStream_t>(stream));
 }
 
 int mxattn_attend(const uint8_t* q_codes, const uint8_t* q_scales, const uint8_t* k_codes,
@@ -527,13 +535,11 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     const size_t q_codes = q_fused ? 0 : mxattn_codes_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nq, d);
     const size_t q_scales = q_fused ? 0 : mxattn_scales_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nq, d);
     const size_t k_codes = mxattn_codes_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nkv, d);
-    const size_t k_scales = mxattn_scales_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nkv, d);
-    const size_t v_codes = mxattn_codes_bytes(MXATTN_AXIS_TOKENS, B, H, Nkv, d);
-    const size_t v_scales = mxattn_scales_bytes(MXATTN_AXIS_TOKENS, B, H, Nkv, d);
+    const int64_t ntiles = (Nkv + mxattn::kKvTile - 1) / mxattn::kKvTile;
+    const size_t v_codes = (size_t)(B * H * ntiles * 8192);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t tiled = (size_t)mxattn::tile_scales_bytes(B * H, Nkv);
-    const size_t total = up(q_codes) + up(k_codes) + up(v_codes) + up(q_scales) + up(k_scales) +
-                         up(v_scales) + up(tiled);
+    const size_t total = up(q_codes) + up(k_codes) + up(v_codes) + up(q_scales) + up(tiled);
 
     void* ws = nullptr;
     hipError_t e = workspace_alloc(&ws, total, s);
@@ -550,25 +556,28 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     p += up(v_codes);
     uint8_t* qs = p;
     p += up(q_scales);
-    uint8_t* ks = p;
-    p += up(k_scales);
-    uint8_t* vs = p;
-    p += up(v_scales);
     uint8_t* sc = p;
 
-    const int rule = rule_of(mode);
+    mxattn::PrepareArgs a{};
+    a.q = q_fused ? nullptr : static_cast<const uint4*>(q);
+    a.k = static_cast<const uint4*>(k);
+    a.v = static_cast<const uint4*>(v);
+    a.qc = qc;
+    a.qs = qs;
+    a.kc = kc;
+    a.vc = vc;
+    a.sc = sc;
+    a.BH = B * H;
+    a.N = (int)Nkv;
+    a.Nq = (int)Nq;
+    a.ntiles = (int)ntiles;
+    a.qtiles = (int)((Nq + 127) / 128);
     int st = MXATTN_OK;
-    auto qk = [mode](const void* x, uint8_t* c, uint8_t* sc, int64_t rows, int rule, hipStream_t st) {
-        return mode == MXATTN_UOS_PNQ_ROT ? mxattn::launch_quantize_headdim_rotated(x, c, sc, rows, rule, st)
-                                          : mxattn::launch_quantize_headdim(x, c, sc, rows, rule, st);
-    };
-    if ((!q_fused && (e = qk(q, qc, qs, B * H * Nq, rule, s)) != hipSuccess) ||
-        (e = qk(k, kc, ks, B * H * Nkv, rule, s)) != hipSuccess ||
-        (e = mxattn::launch_quantize_tokens(v, vc, vs, B * H, Nkv, rule, s)) != hipSuccess) {
+    if ((e = mxattn::launch_prepare_operands(a, rule_of(mode), !q_fused, s)) != hipSuccess) {
         set_error("quantize launch", e);
         st = MXATTN_ERR_HIP;
     } else {
-        st = launch_attend(q_fused ? q : nullptr, qc, qs, kc, ks, vc, vs, sc, out, B, H, Nq, Nkv, mode, s);
+        st = launch_attend(q_fused ? q : nullptr, qc, qs, kc, vc, true, sc, out, B, H, Nq, Nkv, mode, s);
     }
     e = hipFreeAsync(ws, s);
     if (st == MXATTN_OK && e != hipSuccess) {

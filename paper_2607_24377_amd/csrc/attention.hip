@@ -96,14 +96,15 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // last tile, K^ rows of keys past N lie past the end of the head's array and
 // read as zero (buffer range check; their scores are masked anyway); V^ key
 // blocks past the end of a channel row read the start of the next row (zeros
-// after the last row).  Those V^ values meet P^ entries that are zero, and
-// FP4 codes and E8M0 scales are always finite, so they contribute nothing.
+// after the last row; with whole tiles stored, zeros).  Those V^ values meet P^
+// entries that are zero, and FP4 codes and E8M0 scales are always finite, so
+// they contribute nothing.
 struct TileLoader {
     __amdgpu_buffer_rsrc_t kc;  // this head's K^ codes [N, 64]
-    __amdgpu_buffer_rsrc_t vc;  // this head's V^ codes [128, nb * 16]
+    __amdgpu_buffer_rsrc_t vc;  // this head's V^ codes (vhead bytes)
     __amdgpu_buffer_rsrc_t sc;  // this head's operand-order scales [ntiles, 1024]
-    uint32_t koff[2];           // lane offsets (bytes) within a tile
-    uint32_t voff[2];
+    uint32_t koff[2], voff;     // lane offsets (bytes) within a tile
+    int vtile, vstep;           // bytes from tile to tile of V^, from the first load's channels to the second's
     int wave, lane;
 
     // raw buffer, 32-bit data format (word 3 of the gfx9 buffer descriptor)
@@ -113,28 +114,29 @@ struct TileLoader {
         : wave(wave_), lane(lane_) {
         const int ntiles = (a.N + 127) / 128;
         kc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.kc + (int64_t)bh * a.N * 64), 0, a.N * 64, kRsrcFlags);
-        vc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.vc + (int64_t)bh * 128 * a.nb * 16), 0,
-                                               128 * a.nb * 16, kRsrcFlags);
+        vc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.vc + (int64_t)bh * a.vhead), 0, a.vhead, kRsrcFlags);
         sc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.sc + (int64_t)bh * ntiles * 1024), 0, ntiles * 1024,
                                                kRsrcFlags);
-#pragma unroll
-        for (int it = 0; it < 2; it++) {
-            const int p = (2 * wave + it) * 64 + lane;  // 16-byte slot of the region
-            const int row = p >> 2;
-            // K^: LDS row 64 c + 32 j + r is A-row r of the S product for
-            // 32-key tile j of 64-key chunk c, and holds key
-            // 64 c + 32 ((r >> 2) & 1) + 16 j + 4 (r >> 3) + (r & 3).  In the
-            // 32x32 output layout accumulator i of lane (q, h) is A-row
-            // 8 (i / 4) + 4 h + (i % 4), so after both tiles of a chunk lane
-            // (q, h) holds keys 32 h .. 32 h + 31 of the chunk in order.  The
-            // slot is the channel block.  V^: row = channel, slot -> key block
-            // (same swizzle).
-            const int r = row & 31, j = (row >> 5) & 1, c = row >> 6;
-            const int key = 64 * c + 32 * ((r >> 2) & 1) + 16 * j + 4 * (r >> 3) + (r & 3);
-            const int db = (p & 3) ^ swz(row);
-            koff[it] = (uint32_t)(key * 64 + db * 16);
-            voff[it] = (uint32_t)((row * a.nb + db) * 16);
-        }
+        vtile = a.vtile;
+        vstep = 16 * a.vrow;
+        const int row = 32 * wave + (lane >> 2);  // of the first of the wave's two loads, 16-byte slot lane & 3
+        // K^: LDS row 64 c + 32 j + r is A-row r of the S product for
+        // 32-key tile j of 64-key chunk c, and holds key
+        // 64 c + 32 ((r >> 2) & 1) + 16 j + 4 (r >> 3) + (r & 3).  In the
+        // 32x32 output layout accumulator i of lane (q, h) is A-row
+        // 8 (i / 4) + 4 h + (i % 4), so after both tiles of a chunk lane
+        // (q, h) holds keys 32 h .. 32 h + 31 of the chunk in order.  The
+        // slot is the channel block.  V^: row = channel, slot -> key block
+        // (same swizzle).  The second load's rows are 16 further on: the same
+        // swizzle, keys 8 further on.
+        const int r = row & 31, j = (row >> 5) & 1, c = row >> 6;
+        const int key = 64 * c + 32 * ((r >> 2) & 1) + 16 * j + 4 * (r >> 3) + (r & 3);
+        const int db = (lane & 3) ^ swz(row);
+        // (the K^ step is part of the lane offset: a scalar offset past the end
+        // of the array would leave the range check)
+        koff[0] = (uint32_t)(key * 64 + db * 16);
+        koff[1] = koff[0] + 512;
+        voff = (uint32_t)(row * a.vrow + db * 16);
     }
 
     __device__ __forceinline__ void load(uint8_t* st, int tile_) const {
@@ -146,7 +148,7 @@ struct TileLoader {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(kc, (lds_ptr_t)(st + kKcOff + (2 * wave + it) * 1024), 16,
                                                      (int)koff[it], tile * 8192, 0, 0);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(vc, (lds_ptr_t)(st + kVcOff + (2 * wave + it) * 1024), 16,
-                                                     (int)voff[it], tile * 64, 0, 0);
+                                                     (int)voff, tile * vtile + it * vstep, 0, 0);
         }
         if (wave == 0)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(sc, (lds_ptr_t)(st + kKsOff), 16, lane * 16, tile * 1024, 0, 0);

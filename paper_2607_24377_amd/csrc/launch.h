@@ -26,6 +26,21 @@ hipError_t launch_quantize_headdim_rotated(const void* x, uint8_t* codes, uint8_
 hipError_t launch_quantize_tokens(const void* x, uint8_t* codes, uint8_t* scales, int64_t BH,
                                   int64_t N, int rule, hipStream_t stream, double qmax = 0.0);
 
+// The quantized operands of a forward call, in the attention kernel's layouts
+// (AttnArgs), in one launch: K^, V^ and their scales; Q^ too where q is not
+// null (the rotated mode).
+struct PrepareArgs {
+    const uint4 *q, *k, *v;  // bf16 [BH, Nq or N, 128]
+    uint8_t *qc, *qs;        // [BH, Nq, 64], [BH, Nq, 4]
+    uint8_t* kc;             // [BH, N, 64]
+    uint8_t* vc;             // [BH, ntiles, 128, 64]
+    uint8_t* sc;             // [BH, ntiles, 1024]
+    int64_t BH;
+    int N, Nq, ntiles, qtiles;  // tiles of 128 tokens
+    int64_t first;              // set by the launcher: first workgroup of a launch
+};
+hipError_t launch_prepare_operands(const PrepareArgs& a, int rule, bool rotated, hipStream_t stream);
+
 // Per-head squared-error sweep over boundaries (qmax.hip).  The histogram
 // pass writes partial sums to a workspace of qmax_sse_workspace_bytes(...)
 // bytes; the reduction turns them into sse[BH, nq] (fp64).
@@ -39,14 +54,12 @@ struct AttnArgs {
     const uint8_t* qs;  // [BH, Nq, 4]
     const uint16_t* qraw;  // bf16 Q [BH, Nq, 128] if the kernel quantizes Q itself, else null
     const uint8_t* kc;  // [BH, N, 64]
-    const uint8_t* ks;  // [BH, N, 4]
-    const uint8_t* vc;  // [BH, 128, nb * 16]
-    const uint8_t* vs;  // [BH, 128, nb]
+    const uint8_t* vc;  // V^ codes: channel d of tile t at head * vhead + t * vtile + d * vrow, 64 B (16 B per block)
     const uint8_t* sc;  // [BH, ntiles, 1024]: K^ and V^ scales in MFMA operand order
     uint16_t* out;      // [BH, Nq, 128] bf16
     int N;              // keys / values per head
     int Nq;             // queries per head (Q^ codes/scales and out are [BH, Nq, ...])
-    int nb;
+    int vrow, vtile, vhead;  // bytes; [BH, 128, nb * 16] or [BH, ntiles, 128, 64]
     int qtiles;
     int total_tiles;    // workgroups that do work
     int per_xcd;

@@ -63,10 +63,10 @@ __device__ __forceinline__ void butterfly_lanes(float (&y)[8], int t) {
     for (int e = 0; e < 8; e++) y[e] = __builtin_fmaf(sgn, y[e], lane_xor<kM>(y[e]));
 }
 
-// Quantizes the 16-byte chunk v (8 elements) of chunk index i.
+// Quantizes the 16-byte chunk v (8 elements) that this lane holds of its
+// 32-element block (lanes 4 i .. 4 i + 3): its codes; the block's E8M0 byte.
 template <int kRule>
-__device__ __forceinline__ void quantize_chunk(uint4 v, int64_t i, bool valid, uint32_t* __restrict__ codes,
-                                               uint8_t* __restrict__ scales, Boundary bq) {
+__device__ __forceinline__ uint32_t quantize_chunk(uint4 v, Boundary bq, uint32_t& sbyte) {
     // block maximum of |x| on the bf16 bit patterns (order-preserving for
     // nonnegative finite values)
     uint32_t m = 0;
@@ -81,17 +81,14 @@ __device__ __forceinline__ void quantize_chunk(uint4 v, int64_t i, bool valid, u
     m = max(m, (uint32_t)lane_xor<1>((int)m));
     m = max(m, (uint32_t)lane_xor<2>((int)m));
     // all-zero block: sigma = 1 (Algorithm 1); codes come out as signed zeros
-    const uint32_t sbyte = (m == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m, bq) + 127);
+    sbyte = (m == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m, bq) + 127);
     const float sf = e8m0_as_f32(sbyte);
     uint32_t c = 0;
     c = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(c, __builtin_bit_cast(bf16x2, v.x), sf, 0);
     c = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(c, __builtin_bit_cast(bf16x2, v.y), sf, 1);
     c = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(c, __builtin_bit_cast(bf16x2, v.z), sf, 2);
     c = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(c, __builtin_bit_cast(bf16x2, v.w), sf, 3);
-    if (valid) {
-        codes[i] = c;
-        if ((i & 3) == 0) scales[i >> 2] = (uint8_t)sbyte;
-    }
+    return c;
 }
 
 template <int kRule>
@@ -110,7 +107,12 @@ __global__ __launch_bounds__(256) void quantize_headdim_kernel(const uint4* __re
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         const int64_t i = i0 + k * stride;
-        quantize_chunk<kRule>(v[k], i, i < n_chunks, codes, scales, bq);
+        uint32_t sbyte;
+        const uint32_t c = quantize_chunk<kRule>(v[k], bq, sbyte);
+        if (i < n_chunks) {
+            codes[i] = c;
+            if ((i & 3) == 0) scales[i >> 2] = (uint8_t)sbyte;
+        }
     }
 }
 
@@ -127,21 +129,9 @@ __global__ __launch_bounds__(256) void quantize_headdim_kernel(const uint4* __re
 // rounded fp32 add, subtract or multiply in a fixed order, so the result is
 // bit-identical to any other evaluation in that order.
 // ---------------------------------------------------------------------------
+// One lane of a row: elements 16 t .. 16 t + 15 of the row as two chunks.
 template <int kRule>
-__global__ __launch_bounds__(256) void quantize_headdim_rot_kernel(const uint4* __restrict__ x,
-                                                                   uint2* __restrict__ codes,
-                                                                   uint8_t* __restrict__ scales,
-                                                                   int64_t n_threads) {
-    // 8 lanes per row of 128, 16 consecutive elements (two chunks) each
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool valid = g < n_threads;
-    uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
-    if (valid) {
-        v0 = nt_load(x + 2 * g);
-        v1 = nt_load(x + 2 * g + 1);
-    }
-    const int t = threadIdx.x & 7;  // thread within the row: elements 16t..16t+15
-
+__device__ __forceinline__ uint2 quantize_rotated(uint4 v0, uint4 v1, int t, uint32_t& sbyte) {
     float y[16];
     const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
 #pragma unroll
@@ -183,7 +173,7 @@ __global__ __launch_bounds__(256) void quantize_headdim_rot_kernel(const uint4* 
 #pragma unroll
     for (int e = 0; e < 16; e++) m = max(m, __builtin_bit_cast(uint32_t, y[e]) & 0x7FFFFFFFu);
     m = max(m, (uint32_t)lane_xor<1>((int)m));
-    const uint32_t sbyte = (m == 0) ? 127u : (uint32_t)(scale_exponent_f32<kRule>(m) + 127);
+    sbyte = (m == 0) ? 127u : (uint32_t)(scale_exponent_f32<kRule>(m) + 127);
     const float sf = e8m0_as_f32(sbyte);
 
     uint32_t c0 = 0, c1 = 0;
@@ -195,8 +185,26 @@ __global__ __launch_bounds__(256) void quantize_headdim_rot_kernel(const uint4* 
     c1 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c1, y[10], y[11], sf, 1);
     c1 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c1, y[12], y[13], sf, 2);
     c1 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c1, y[14], y[15], sf, 3);
+    return make_uint2(c0, c1);
+}
+
+template <int kRule>
+__global__ __launch_bounds__(256) void quantize_headdim_rot_kernel(const uint4* __restrict__ x,
+                                                                   uint2* __restrict__ codes,
+                                                                   uint8_t* __restrict__ scales,
+                                                                   int64_t n_threads) {
+    // 8 lanes per row of 128, 16 consecutive elements (two chunks) each
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool valid = g < n_threads;
+    uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
     if (valid) {
-        codes[g] = make_uint2(c0, c1);
+        v0 = nt_load(x + 2 * g);
+        v1 = nt_load(x + 2 * g + 1);
+    }
+    uint32_t sbyte;
+    const uint2 c = quantize_rotated<kRule>(v0, v1, threadIdx.x & 7, sbyte);
+    if (valid) {
+        codes[g] = c;
         if ((g & 1) == 0) scales[g >> 1] = (uint8_t)sbyte;
     }
 }
@@ -229,6 +237,34 @@ __device__ __forceinline__ uint32_t cvt_fp4x2_bf16(uint32_t old, uint32_t pair, 
         case 2: return __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(old, v, scale, 2);
         default: return __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(old, v, scale, 3);
     }
+}
+
+// The 32-token blocks of two channels (the low and high halves of col[t], t
+// the token in the block): codes and E8M0 bytes of each.
+template <int kRule>
+__device__ __forceinline__ void quantize_token_pair(const uint32_t (&col)[32], Boundary bq, uint4& c0, uint4& c1,
+                                                    uint32_t& s0, uint32_t& s1) {
+    uint32_t m0 = 0, m1 = 0;
+#pragma unroll
+    for (int t = 0; t < 32; t++) {
+        m0 = max(m0, col[t] & 0x7FFFu);
+        m1 = max(m1, (col[t] >> 16) & 0x7FFFu);
+    }
+    s0 = (m0 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m0, bq) + 127);
+    s1 = (m1 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m1, bq) + 127);
+    const float f0 = e8m0_as_f32(s0), f1 = e8m0_as_f32(s1);
+    uint32_t a[4] = {0, 0, 0, 0}, b[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 32; t += 2) {
+        // (token t, token t+1) pairs of each channel
+        const uint32_t lo = __builtin_amdgcn_perm(col[t + 1], col[t], 0x05040100u);  // low halves
+        const uint32_t hi = __builtin_amdgcn_perm(col[t + 1], col[t], 0x07060302u);  // high halves
+        const int word = t >> 3, sel = (t & 7) >> 1;
+        a[word] = cvt_fp4x2_bf16(a[word], lo, f0, sel);
+        b[word] = cvt_fp4x2_bf16(b[word], hi, f1, sel);
+    }
+    c0 = make_uint4(a[0], a[1], a[2], a[3]);
+    c1 = make_uint4(b[0], b[1], b[2], b[3]);
 }
 
 template <int kRule>
@@ -287,35 +323,174 @@ __global__ __launch_bounds__(kVqThreads) void quantize_tokens_kernel(const uint4
         const int blk = 8 * g + b;
         if (blk < nb) {
             uint32_t col[32];
-            uint32_t m0 = 0, m1 = 0;
 #pragma unroll
-            for (int t = 0; t < 32; t++) {
-                uint32_t d = tile[(32 * b + t) * 64 + (cp ^ (8 * b))];
-                col[t] = d;
-                m0 = max(m0, d & 0x7FFFu);
-                m1 = max(m1, (d >> 16) & 0x7FFFu);
-            }
-            const uint32_t s0 = (m0 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m0, bq) + 127);
-            const uint32_t s1 = (m1 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m1, bq) + 127);
-            const float f0 = e8m0_as_f32(s0), f1 = e8m0_as_f32(s1);
-
-            uint32_t c0[4] = {0, 0, 0, 0}, c1[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int t = 0; t < 32; t += 2) {
-                // (token t, token t+1) pairs of each channel
-                uint32_t lo = __builtin_amdgcn_perm(col[t + 1], col[t], 0x05040100u);  // low halves
-                uint32_t hi = __builtin_amdgcn_perm(col[t + 1], col[t], 0x07060302u);  // high halves
-                const int word = t >> 3, sel = (t & 7) >> 1;
-                c0[word] = cvt_fp4x2_bf16(c0[word], lo, f0, sel);
-                c1[word] = cvt_fp4x2_bf16(c1[word], hi, f1, sel);
-            }
+            for (int t = 0; t < 32; t++) col[t] = tile[(32 * b + t) * 64 + (cp ^ (8 * b))];
+            uint4 c0, c1;
+            uint32_t s0, s1;
+            quantize_token_pair<kRule>(col, bq, c0, c1, s0, s1);
             const int64_t row0 = (int64_t)bh * 128 + 2 * cp;
-            *reinterpret_cast<uint4*>(codes + (row0 * nb + blk) * 16) = make_uint4(c0[0], c0[1], c0[2], c0[3]);
-            *reinterpret_cast<uint4*>(codes + ((row0 + 1) * nb + blk) * 16) = make_uint4(c1[0], c1[1], c1[2], c1[3]);
+            *reinterpret_cast<uint4*>(codes + (row0 * nb + blk) * 16) = c0;
+            *reinterpret_cast<uint4*>(codes + ((row0 + 1) * nb + blk) * 16) = c1;
             scales[row0 * nb + blk] = (uint8_t)s0;
             scales[(row0 + 1) * nb + blk] = (uint8_t)s1;
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// The operands of a forward call in one launch: K along the channels, V along
+// the tokens and, in the rotated mode, Q, in the layouts the attention kernel
+// reads.  A workgroup takes one 128-token tile of one tensor and head (32 KiB
+// of bf16, loaded at once: 128 bytes in flight per thread):
+//   V  codes as [head][tile][channel][64 B] (8 KiB per workgroup, contiguous;
+//      the public layout's 128 channel rows lie 38 KB apart at 720p), staged
+//      through LDS as quantize_tokens_kernel does it, one lane per channel
+//      pair and block;
+//   K  codes as [head][key][64 B];
+//   both write their scales in the MFMA operand order of the attention kernel
+//      (tile_scales_kernel), K^'s gathered in LDS first, 127 for keys and
+//      blocks past the end (their products meet masked scores or zero P^);
+//   Q  rotated, codes and scales in the public layout.
+// One launch instead of three (four in the rotated mode) and no pass over the
+// scales: the short calls wait for launches (2 heads x 512 tokens: the whole
+// forward 37 -> 29 us), the long ones are bound by HBM (K and V at 720p: 349 us
+// as three launches, 313 us = 6.3 TB/s as one).  The attention kernel also
+// reads whole 8 KiB V^ tiles faster than 128 rows of 64 bytes (720p forward
+// 44.8 -> 43.5 ms).
+constexpr int kPrepThreads = 256;
+
+// Byte of a tile's K^ scales that holds channel block db of key w: lane
+// r + 32 (db & 1), byte 4 c + 2 j + (db >> 1) for A-row r of score product
+// (chunk c, tile j).
+__device__ __forceinline__ int k_scale_slot(int w, int db) {
+    const int r = (w & 3) | (((w >> 2) & 3) << 3) | (((w >> 5) & 1) << 2);
+    return (r + 32 * (db & 1)) * 8 + 4 * (w >> 6) + 2 * ((w >> 4) & 1) + (db >> 1);
+}
+
+template <int kRule, bool kRot>
+__global__ __launch_bounds__(kPrepThreads) void prepare_operands_kernel(PrepareArgs a) {
+    __shared__ __attribute__((aligned(16))) uint32_t tile[128 * 64];
+    const int tid = threadIdx.x;
+    // tiles of V first, then K, then (rotated) Q
+    int64_t wg = a.first + blockIdx.x;
+    const int64_t kv_wgs = a.BH * a.ntiles;
+    const int role = wg < kv_wgs ? 0 : (wg < 2 * kv_wgs ? 1 : 2);
+    wg -= role * kv_wgs;
+    const int nt = role == 2 ? a.qtiles : a.ntiles;
+    const int N = role == 2 ? a.Nq : a.N;
+    const int64_t bh = wg / nt;
+    const int t = (int)(wg - bh * nt);
+    const int rows = min(128, N - t * 128);
+    const int64_t row0 = bh * N + t * 128;  // first token of the tile
+    const uint4* x = (role == 0 ? a.v : (role == 1 ? a.k : a.q)) + row0 * 16;
+
+    if (role == 0) {
+        uint4 buf[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int ch = tid + kPrepThreads * k;
+            buf[k] = (ch >> 4) < rows ? nt_load(x + ch) : make_uint4(0, 0, 0, 0);
+        }
+        // [token][64 dwords]; block b's dword columns XOR-ed by 16 b, so the
+        // four blocks' lanes read different banks
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int ch = tid + kPrepThreads * k;
+            const int tok = ch >> 4, part = ch & 15;
+            *reinterpret_cast<uint4*>(&tile[tok * 64 + ((part * 4) ^ (16 * (tok >> 5)))]) = buf[k];
+        }
+        __syncthreads();
+        const int b = tid & 3, cp = tid >> 2;  // block of the tile, channel pair
+        uint32_t col[32];
+#pragma unroll
+        for (int i = 0; i < 32; i++) col[i] = tile[(32 * b + i) * 64 + (cp ^ (16 * b))];
+        uint4 c0, c1;
+        uint32_t s0, s1;
+        quantize_token_pair<kRule>(col, Boundary{}, c0, c1, s0, s1);
+        uint8_t* dst = a.vc + (bh * a.ntiles + t) * 8192 + cp * 128 + b * 16;
+        *reinterpret_cast<uint4*>(dst) = c0;
+        *reinterpret_cast<uint4*>(dst + 64) = c1;
+        // channel d: lane (d & 31) + 32 (b & 1), byte 2 (d >> 5) + (b >> 1)
+        const int d = 2 * cp;
+        uint8_t* sc = a.sc + (bh * a.ntiles + t) * 1024 + 512 + ((d & 31) + 32 * (b & 1)) * 8 + 2 * (d >> 5) + (b >> 1);
+        sc[0] = (uint8_t)s0;
+        sc[8] = (uint8_t)s1;
+        return;
+    }
+
+    uint8_t* const slds = reinterpret_cast<uint8_t*>(tile);  // the tile's K^ scales
+    if (role == 1) {
+        if (tid < 128) tile[tid] = 0x7F7F7F7Fu;
+        __syncthreads();
+    }
+    uint8_t* const codes = (role == 1 ? a.kc : a.qc) + row0 * 64;
+    if constexpr (kRot) {
+        // 8 lanes per row, 16 elements each
+        uint4 v[4][2];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int i = tid + kPrepThreads * k;
+            const bool ok = (i >> 3) < rows;
+#pragma unroll
+            for (int e = 0; e < 2; e++) v[k][e] = ok ? nt_load(x + 2 * i + e) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int i = tid + kPrepThreads * k;
+            const int row = i >> 3, db = (i & 7) >> 1;
+            uint32_t sbyte;
+            const uint2 c = quantize_rotated<kRule>(v[k][0], v[k][1], i & 7, sbyte);
+            if (row < rows) {
+                reinterpret_cast<uint2*>(codes)[i] = c;
+                if ((i & 1) == 0) {
+                    if (role == 1)
+                        slds[k_scale_slot(row, db)] = (uint8_t)sbyte;
+                    else
+                        a.qs[(row0 + row) * 4 + db] = (uint8_t)sbyte;
+                }
+            }
+        }
+    } else {
+        // 16 lanes per row, one chunk each
+        uint4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int i = tid + kPrepThreads * k;
+            v[k] = (i >> 4) < rows ? nt_load(x + i) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int i = tid + kPrepThreads * k;
+            const int row = i >> 4;
+            uint32_t sbyte;
+            const uint32_t c = quantize_chunk<kRule>(v[k], Boundary{}, sbyte);
+            if (row < rows) {
+                reinterpret_cast<uint32_t*>(codes)[i] = c;
+                if ((i & 3) == 0) slds[k_scale_slot(row, (i & 15) >> 2)] = (uint8_t)sbyte;
+            }
+        }
+    }
+    if (role == 1) {
+        __syncthreads();
+        if (tid < 128) reinterpret_cast<uint32_t*>(a.sc + (bh * a.ntiles + t) * 1024)[tid] = tile[tid];
+    }
+}
+
+hipError_t launch_prepare_operands(const PrepareArgs& args, int rule, bool rotated, hipStream_t stream) {
+    const int64_t wgs = args.BH * (2 * (int64_t)args.ntiles + (args.q ? args.qtiles : 0));
+    constexpr int64_t kMost = (int64_t)1 << 23;  // workgroups of one launch (2^31 threads)
+    PrepareArgs a = args;
+    for (a.first = 0; a.first < wgs; a.first += kMost) {
+        const dim3 grid((unsigned)(wgs - a.first < kMost ? wgs - a.first : kMost));
+        if (rotated)  // the rotated mode's rule is UOS
+            prepare_operands_kernel<kRuleUos, true><<<grid, kPrepThreads, 0, stream>>>(a);
+        else if (rule == kRuleUos)
+            prepare_operands_kernel<kRuleUos, false><<<grid, kPrepThreads, 0, stream>>>(a);
+        else
+            prepare_operands_kernel<kRuleOcp, false><<<grid, kPrepThreads, 0, stream>>>(a);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 // Kernel argument of the kRuleQmax rule for boundary q (4 <= q <= 8).

@@ -186,6 +186,28 @@ def test_attend_matches_forward_and_is_deterministic(mx):
         assert torch.equal(a.view(torch.int16), c.view(torch.int16))
 
 
+@pytest.mark.parametrize("Nq,Nkv", [(1, 1), (129, 127), (127, 129), (300, 513), (33, 1025)])
+def test_forward_operands_equal_the_public_ones(mx, Nq, Nkv):
+    """The forward quantizes K and V (and the rotated mode's Q) in one launch,
+    tile by tile and with the scales in operand order; its output must equal
+    the kernel run on the standalone quantizers' codes, bit for bit, with
+    ragged and whole last tiles, several heads and all modes."""
+    q = inputs.generate(inputs.custom(2, 3, Nq, kind="video", index=73))[0]
+    _, k, v = inputs.generate(inputs.custom(2, 3, Nkv, kind="video", index=74))
+    k[:, :, 0, :32] = 0  # an all-zero block of K and of V
+    v[:, :, : min(32, Nkv), 5] = 0
+    qt, kt, vt = (mx.bf16_from_bits(x) for x in (q, k, v))
+    for mode in MODES + ["uos_pnq_rot"]:
+        a = mx.cross_forward(qt, kt, vt, mode)
+        qc, qs = mx.quantize(qt, mx.AXIS_HEAD_DIM, mode)
+        kc, ks = mx.quantize(kt, mx.AXIS_HEAD_DIM, mode)
+        vc, vs = mx.quantize(vt, mx.AXIS_TOKENS, mode)
+        b = mx.cross_attend(qc, qs, kc, ks, vc, vs, Nq, Nkv, mode)
+        torch.cuda.synchronize()
+        log(f"[attn] forward operands Nq={Nq} Nkv={Nkv} mode={mode}")
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (Nq, Nkv, mode)
+
+
 def _edge_q_rows(q):
     """Overwrite the first query rows of every head with values that exercise
     the quantizer's scale rule: an all-zero block (sigma = 1), bf16
