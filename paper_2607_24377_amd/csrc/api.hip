@@ -325,8 +325,8 @@ int check_attention_shape(int64_t B, int64_t H, int64_t Nq, int64_t Nkv) {
 // holds the K^/V^ scales in operand order.  v_tiled: V^ codes stored tile by
 // tile (launch_prepare_operands) instead of in channel rows.
 static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs, const uint8_t* kc,
-                         const uint8_t* vc, bool v_tiled, const uint8_t* sc, void* out, int64_t B, int64_t H,
-                         int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
+                         const uint8_t* vc, bool v_tiled, const uint8_t* sc, uint8_t* split_ws, void* out,
+                         int64_t B, int64_t H, int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
     mxattn::AttnArgs a;
     a.qc = qc;
     a.qs = qs;
@@ -354,7 +354,13 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
         nchunks = k < min_chunks ? min_chunks : (k > a.qtiles ? a.qtiles : k);
     }
     a.nchunks = (int)nchunks;
-    const int64_t total = B * H * a.nchunks;
+    a.nsplit = mxattn::key_splits(B * H, Nq, Nkv);
+    const int64_t total = B * H * a.nchunks * a.nsplit;
+    if (a.nsplit > 1) {
+        a.part_o = reinterpret_cast<float4*>(split_ws);
+        a.part_ml = reinterpret_cast<float2*>(split_ws + total * (128 * 128 * 4));
+        a.run_max = reinterpret_cast<float*>(split_ws + total * (128 * (128 * 4 + 8)));
+    }
     a.total_tiles = (int)total;
     a.per_xcd = (int)((total + 7) / 8);
     hipError_t e = mxattn::launch_attention(a, kernel_mode(mode), s);
@@ -368,14 +374,14 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
 // The same on operands in the public layouts: rearranges the K^/V^ scales into
 // sc (mxattn::tile_scales_bytes(B*H, Nkv) bytes of workspace) first.
 static int launch_attend_public(const uint8_t* qc, const uint8_t* qs, const uint8_t* kc, const uint8_t* ks,
-                                const uint8_t* vc, const uint8_t* vs, uint8_t* sc, void* out, int64_t B,
-                                int64_t H, int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
+                                const uint8_t* vc, const uint8_t* vs, uint8_t* sc, uint8_t* split_ws, void* out,
+                                int64_t B, int64_t H, int64_t Nq, int64_t Nkv, int mode, hipStream_t s) {
     hipError_t e = mxattn::launch_tile_scales(ks, vs, sc, B * H, Nkv, s);
     if (e != hipSuccess) {
         set_error("scale layout launch", e);
         return MXATTN_ERR_HIP;
     }
-    return launch_attend(nullptr, qc, qs, kc, vc, false, sc, out, B, H, Nq, Nkv, mode, s);
+    return launch_attend(nullptr, qc, qs, kc, vc, false, sc, split_ws, out, B, H, Nq, Nkv, mode, s);
 }
 
 // Whether `out` ([B, H, Nq, d] bf16) shares memory with any quantized operand.
@@ -419,13 +425,16 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
         return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     void* ws = nullptr;
-    hipError_t e = workspace_alloc(&ws, (size_t)mxattn::tile_scales_bytes(B * H, Nkv), s);
+    const size_t scale_bytes = (size_t)mxattn::tile_scales_bytes(B * H, Nkv);
+    hipError_t e =
+        workspace_alloc(&ws, scale_bytes + mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv)), s);
     if (e != hipSuccess || !ws) {
         set_error("workspace allocation", e);
         return MXATTN_ERR_OOM;
     }
     int st = launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales,
-                                  static_cast<uint8_t*>(ws), out, B, H, Nq, Nkv, mode, s);
+                                  static_cast<uint8_t*>(ws), static_cast<uint8_t*>(ws) + scale_bytes, out, B, H, Nq,
+                                  Nkv, mode, s);
     e = hipFreeAsync(ws, s);
     if (st == MXATTN_OK && e != hipSuccess) {
         set_error("hipFreeAsync", e);
@@ -439,13 +448,14 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
 // mxattn_cross_attend_noalloc keeps its one buffer beyond the inputs and the
 // output, the K^/V^ scales rearranged into MFMA operand order (1 KiB per
 // (batch, head) and 128-key tile), in this static device array instead of
-// allocated workspace.  Each device the library runs on holds its own copy
+// allocated workspace, with the partial results of divided keys behind it.  Each device the library runs on holds its own copy
 // until the process ends.  On the host, `scratch` is only a stand-in symbol,
 // never a device address: the device address comes from hipGetSymbolAddress,
 // taken once per device with that device current, and only that address is
 // passed to kernels.  Every call on a device shares the device's array, so
 // calls that overlap in time on one device race.
-static __device__ __align__(256) uint8_t scratch[MXATTN_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) uint8_t scratch[MXATTN_NOALLOC_SCRATCH_BYTES +
+                                                  mxattn::kMaxSplitWorkgroups * mxattn::kSplitBytesPerWorkgroup];
 
 struct ScratchSlot {
     std::once_flag once;
@@ -502,7 +512,8 @@ int mxattn_cross_attend_noalloc(const uint8_t* q_codes, const uint8_t* q_scales,
     void* sc = nullptr;
     if (int st = scratch_address(&sc)) return st;
     return launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales, static_cast<uint8_t*>(sc),
-                                out, B, H, Nq, Nkv, mode, reinterpret_cast<hipStream_t>(stream));
+                                static_cast<uint8_t*>(sc) + MXATTN_NOALLOC_SCRATCH_BYTES, out, B, H, Nq, Nkv, mode,
+                                reinterpret_cast<hipStream_t>(stream));
 }
 
 int mxattn_attend(const uint8_t* q_codes, const uint8_t* q_scales, const uint8_t* k_codes,
@@ -539,7 +550,8 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     const size_t v_codes = (size_t)(B * H * ntiles * 8192);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t tiled = (size_t)mxattn::tile_scales_bytes(B * H, Nkv);
-    const size_t total = up(q_codes) + up(k_codes) + up(v_codes) + up(q_scales) + up(tiled);
+    const size_t split = mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv));
+    const size_t total = up(q_codes) + up(k_codes) + up(v_codes) + up(q_scales) + up(tiled) + split;
 
     void* ws = nullptr;
     hipError_t e = workspace_alloc(&ws, total, s);
@@ -577,7 +589,7 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
         set_error("quantize launch", e);
         st = MXATTN_ERR_HIP;
     } else {
-        st = launch_attend(q_fused ? q : nullptr, qc, qs, kc, vc, true, sc, out, B, H, Nq, Nkv, mode, s);
+        st = launch_attend(q_fused ? q : nullptr, qc, qs, kc, vc, true, sc, sc + up(tiled), out, B, H, Nq, Nkv, mode, s);
     }
     e = hipFreeAsync(ws, s);
     if (st == MXATTN_OK && e != hipSuccess) {

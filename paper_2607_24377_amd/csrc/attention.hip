@@ -110,13 +110,16 @@ struct TileLoader {
     // raw buffer, 32-bit data format (word 3 of the gfx9 buffer descriptor)
     static constexpr int kRsrcFlags = 0x00020000;
 
-    __device__ __forceinline__ TileLoader(const AttnArgs& a, int bh, int wave_, int lane_)
+    // tile 0 of the loader is tile t0 of the head
+    __device__ __forceinline__ TileLoader(const AttnArgs& a, int bh, int t0, int wave_, int lane_)
         : wave(wave_), lane(lane_) {
         const int ntiles = (a.N + 127) / 128;
-        kc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.kc + (int64_t)bh * a.N * 64), 0, a.N * 64, kRsrcFlags);
-        vc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.vc + (int64_t)bh * a.vhead), 0, a.vhead, kRsrcFlags);
-        sc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.sc + (int64_t)bh * ntiles * 1024), 0, ntiles * 1024,
-                                               kRsrcFlags);
+        kc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.kc + (int64_t)bh * a.N * 64 + (int64_t)t0 * 8192), 0,
+                                               a.N * 64 - t0 * 8192, kRsrcFlags);
+        vc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.vc + (int64_t)bh * a.vhead + (int64_t)t0 * a.vtile), 0,
+                                               a.vhead - t0 * a.vtile, kRsrcFlags);
+        sc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.sc + ((int64_t)bh * ntiles + t0) * 1024), 0,
+                                               (ntiles - t0) * 1024, kRsrcFlags);
         vtile = a.vtile;
         vstep = 16 * a.vrow;
         const int row = 32 * wave + (lane >> 2);  // of the first of the wave's two loads, 16-byte slot lane & 3
@@ -137,6 +140,17 @@ struct TileLoader {
         koff[0] = (uint32_t)(key * 64 + db * 16);
         koff[1] = koff[0] + 512;
         voff = (uint32_t)(row * a.vrow + db * 16);
+    }
+
+    // K^ codes and both scales only (the score pass of split keys)
+    __device__ __forceinline__ void load_k(uint8_t* st, int tile_) const {
+        const int tile = __builtin_amdgcn_readfirstlane(tile_);
+#pragma unroll
+        for (int it = 0; it < 2; it++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(kc, (lds_ptr_t)(st + kKcOff + (2 * wave + it) * 1024), 16,
+                                                     (int)koff[it], tile * 8192, 0, 0);
+        if (wave == 0)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(sc, (lds_ptr_t)(st + kKsOff), 16, lane * 16, tile * 1024, 0, 0);
     }
 
     __device__ __forceinline__ void load(uint8_t* st, int tile_) const {
@@ -525,45 +539,49 @@ __device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo
 // of its query row.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
+// The row sum of this lane's query row.
+template <bool kPnq>
+__device__ __forceinline__ float row_total(const RowSum& rs, int q) {
+    if (kPnq) {
+        // the sums of queries q and q + 16 sit in lane q & 15 (RowSum)
+        const float l0 = __shfl(rs.L[0], q & 15), l1 = __shfl(rs.L[1], q & 15);
+        return q < 16 ? l0 : l1;
+    }
+    return rs.l + __shfl_xor(rs.l, 32);
+}
+
+// Channels 32 n + 8 g + 4 h .. + 3 of the row (O[4 g .. 4 g + 3]) times inv as
+// bf16 pairs w[g] (round to nearest even with the packed hardware
+// conversion).  Lanes q and q + 32 hold the row's channel groups 8 g .. 8 g + 7
+// in halves; swapping the lanes 32-63 of the even-g words with the lanes 0-31
+// of the odd-g words gives lane h all eight channels of group g = 2 j + h,
+// i.e. 16 contiguous bytes (w[2 j], w[2 j + 1]) at channel 32 n + 16 j + 8 h.
+__device__ __forceinline__ void pack_channels(const v16f& O, float inv, uint32_t (&w)[4][2]) {
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        const f32x2 lo = {O[4 * g + 0] * inv, O[4 * g + 1] * inv};
+        const f32x2 hi = {O[4 * g + 2] * inv, O[4 * g + 3] * inv};
+        w[g][0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+        w[g][1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
+    }
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const auto r = __builtin_amdgcn_permlane32_swap(w[2 * j][k], w[2 * j + 1][k], false, false);
+            w[2 * j][k] = (uint32_t)r[0];
+            w[2 * j + 1][k] = (uint32_t)r[1];
+        }
+}
+
 template <bool kPnq>
 __device__ __forceinline__ void store_rows(const AttnArgs& a, int64_t rowbase, int qi, int q, int h, int lane,
                                            uint8_t* stage, bool staged, const RowSum& rs,
                                            const v16f (&O)[4]) {
-    float ltot;
-    if (kPnq) {
-        // the sums of queries q and q + 16 sit in lane q & 15 (RowSum)
-        const float l0 = __shfl(rs.L[0], q & 15), l1 = __shfl(rs.L[1], q & 15);
-        ltot = q < 16 ? l0 : l1;
-    } else {
-        ltot = rs.l + __shfl_xor(rs.l, 32);
-    }
-    const float inv = 1.0f / ltot;  // one division, then 64 products
-    // w[n][g]: channels 32 n + 8 g + 4 h .. + 3 of the row as two bf16 pairs
-    // (round to nearest even with the packed hardware conversion)
+    const float inv = 1.0f / row_total<kPnq>(rs, q);  // one division, then 64 products
     uint32_t w[4][4][2];
 #pragma unroll
-    for (int n = 0; n < 4; n++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-            const f32x2 lo = {O[n][4 * g + 0] * inv, O[n][4 * g + 1] * inv};
-            const f32x2 hi = {O[n][4 * g + 2] * inv, O[n][4 * g + 3] * inv};
-            w[n][g][0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
-            w[n][g][1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-        }
-    // Lanes q and q + 32 hold the row's channel groups 8 g .. 8 g + 7 in
-    // halves.  Swapping the lanes 32-63 of the even-g words with the lanes
-    // 0-31 of the odd-g words gives lane h all eight channels of group
-    // g = 2 j + h, i.e. 16 contiguous bytes per (n, j).
-#pragma unroll
-    for (int n = 0; n < 4; n++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const auto r = __builtin_amdgcn_permlane32_swap(w[n][2 * j][k], w[n][2 * j + 1][k], false, false);
-                w[n][2 * j][k] = (uint32_t)r[0];
-                w[n][2 * j + 1][k] = (uint32_t)r[1];
-            }
+    for (int n = 0; n < 4; n++) pack_channels(O[n], inv, w[n]);
     if (!staged) {
         if (qi < a.Nq) {
             uint16_t* dst = a.out + (rowbase + qi) * 128 + 8 * h;
@@ -716,6 +734,16 @@ __device__ __forceinline__ uint32_t block_scale(float bmax, float m_new) {
     return p_scale_bits<kRule>(__builtin_bit_cast(uint32_t, mb));
 }
 
+// Run s of a head's key tiles: tiles first .. first + tiles - 1.
+struct SplitRange {
+    int first, tiles;
+};
+__device__ __forceinline__ SplitRange split_range(const AttnArgs& a, int s) {
+    const int nt = (a.N + 127) / 128;  // nt * nsplit < 2^26
+    const int first = nt * s / a.nsplit;
+    return {first, nt * (s + 1) / a.nsplit - first};
+}
+
 // State a wave carries from one KV tile to the next.
 struct PipeState {
     v16f S[2][2];  // scores of the current tile
@@ -843,7 +871,10 @@ __device__ __forceinline__ void pipe_tile(uint8_t* const (&stages)[kPipeStages],
     if (!kPnq) ps.rs.l = alpha * ps.rs.l + lsum;
 }
 
-template <int kRule, bool kPnq, bool kQraw>
+// kSplit: the head's keys are divided into a.nsplit runs of tiles, one
+// workgroup each (see split_scores_kernel): this one starts from the largest
+// score of the runs before it and leaves O~, m and l for split_combine_kernel.
+template <int kRule, bool kPnq, bool kQraw, bool kSplit>
 __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t st0[kStageBytes];
     __shared__ __attribute__((aligned(16))) uint8_t st1[kStageBytes];
@@ -857,16 +888,18 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
     const int L = blockIdx.x;
     const int logical = (L & 7) * a.per_xcd + (L >> 3);
     if (logical >= a.total_tiles) return;
-    const int bh = logical / a.qtiles;
-    const int qt = logical - bh * a.qtiles;
-    const int N = a.N;
+    const int run = logical / a.qtiles;  // (head, run of keys)
+    const int qt = logical - run * a.qtiles;
+    const int bh = kSplit ? run / a.nsplit : run;
+    const SplitRange sr = kSplit ? split_range(a, run - bh * a.nsplit) : SplitRange{0, (a.N + 127) / 128};
+    const int N = a.N - sr.first * 128;  // keys from the first tile on
     const int Nq = a.Nq;
     const int64_t rowbase = (int64_t)bh * Nq;
     const int qi = qt * kQueryTile + wave * kQw + q;
     const int qic = min(qi, Nq - 1);
-    const int ntiles = (N + 127) / 128;
+    const int ntiles = sr.tiles;
 
-    const TileLoader loader(a, bh, wave, lane);
+    const TileLoader loader(a, bh, sr.first, wave, lane);
     loader.load(st0, 0);
     if (ntiles > 1) loader.load(st1, 1);
 
@@ -880,6 +913,21 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
 
     PipeState ps;
     ps.m = ps.smax = -__builtin_inff();
+    if constexpr (kSplit) {
+        const int s = run - bh * a.nsplit;
+        if (s > 0) {
+            const float* prior = a.run_max + ((int64_t)bh * a.qtiles + qt) * a.nsplit * kQueryTile + wave * kQw + q;
+            float x = prior[0];
+            for (int i = 1; i < s; i += 4) {
+                // past the last one before s the last is read again
+                const float y0 = prior[i * kQueryTile], y1 = prior[min(i + 1, s - 1) * kQueryTile];
+                const float y2 = prior[min(i + 2, s - 1) * kQueryTile], y3 = prior[min(i + 3, s - 1) * kQueryTile];
+                x = max2f(max3f(x, y0, y1), max2f(y2, y3));
+            }
+            ps.smax = x;
+            ps.m = mul_rd(0.12751743082459868f, x);
+        }
+    }
     ps.rs.l = 0.f;
     ps.rs.L = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -914,7 +962,123 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
     pv_chunk<kPnq, 1>(v_operands<1>(last == 0 ? st0 : (last == 1 ? st1 : st2), lo), ps.P1, ps.psc1, ps.vsb1, sel,
                       ps.rs, ps.O);
 
-    store_rows<kPnq>(a, rowbase, qi, q, h, lane, nullptr, false, ps.rs, ps.O);
+    if constexpr (kSplit) {
+        const int64_t part = ((int64_t)bh * a.qtiles + qt) * a.nsplit + (run - bh * a.nsplit);
+        const float l = row_total<kPnq>(ps.rs, q);
+        if (h == 0) a.part_ml[part * kQueryTile + wave * kQw + q] = make_float2(ps.m, l);
+        float4* dst = a.part_o + (part * kWaves + wave) * 1024 + lane;
+#pragma unroll
+        for (int n = 0; n < 4; n++)
+#pragma unroll
+            for (int g = 0; g < 4; g++)
+                dst[(4 * n + g) * 64] =
+                    make_float4(ps.O[n][4 * g], ps.O[n][4 * g + 1], ps.O[n][4 * g + 2], ps.O[n][4 * g + 3]);
+    } else {
+        store_rows<kPnq>(a, rowbase, qi, q, h, lane, nullptr, false, ps.rs, ps.O);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Few query tiles over long key sequences (a text segment's queries, a GPU's
+// share of the heads, one clip's frame): the keys of a head are divided into
+// a.nsplit runs of whole tiles so that the chip's workgroup slots fill.  P^
+// depends on the running maximum of all earlier keys, so the runs cannot
+// simply start at m = -inf: this pass finds the largest score of every run
+// but the last (scores only: 8 of a tile's 18 products and none of the
+// exponentials, about a fifth of its time), each run of the main pass then
+// starts from the maximum of the runs before it, so every m, P~ and P^ is
+// that of the undivided loop bit for bit, and split_combine_kernel adds the
+// runs' O~ and l, scaled to the last run's maximum: only the association of
+// these fp32 sums differs.
+template <int kRule, bool kQraw>
+__global__ __launch_bounds__(kThreads, 2) void split_scores_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t st0[kStageBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t st1[kStageBytes];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int q = lane & 31, h = lane >> 5;
+    const int runs = a.nsplit - 1;
+    const int L = blockIdx.x;
+    const int per_xcd = (a.total_tiles / a.nsplit * runs + 7) / 8;
+    const int logical = (L & 7) * per_xcd + (L >> 3);
+    if (logical >= a.total_tiles / a.nsplit * runs) return;
+    const int run = logical / a.qtiles;
+    const int qt = logical - run * a.qtiles;
+    const int bh = run / runs, s = run - bh * runs;
+    const SplitRange sr = split_range(a, s);
+    const int64_t row = (int64_t)bh * a.Nq + min(qt * kQueryTile + wave * kQw + q, a.Nq - 1);
+
+    const TileLoader loader(a, bh, sr.first, wave, lane);
+    loader.load_k(st0, 0);
+    QOperands qo;
+    if constexpr (kQraw)
+        qo = quantize_q<kRule>(q_raw(a, row, h));
+    else
+        qo = q_operands(a, row, h);
+    const LaneOff lo = lane_off(q, h, lane);
+    // whole tiles only: the last run is not scored, so no key is masked
+    float x = -__builtin_inff();
+    auto score = [&](const uint8_t* st) {
+        const uint2 ksb = ld64<kKsOff>(st, lo.sc);
+        const KOperands k = k_operands(st, lo);
+        const v16f s00 = score_pair<0, 0>(k, qo, ksb), s01 = score_pair<0, 1>(k, qo, ksb);
+        const v16f s10 = score_pair<1, 0>(k, qo, ksb), s11 = score_pair<1, 1>(k, qo, ksb);
+        x = max3f(x, block_max32(s00, s01), block_max32(s10, s11));
+    };
+    for (int j = 0;; j += 2) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();  // tile j landed, tile j - 1's stage is free
+        if (j + 1 < sr.tiles) loader.load_k(st1, j + 1);
+        score(st0);
+        if (j + 1 >= sr.tiles) break;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (j + 2 < sr.tiles) loader.load_k(st0, j + 2);
+        score(st1);
+        if (j + 2 >= sr.tiles) break;
+    }
+    x = max_with_other_half(x);
+    if (h == 0) a.run_max[(((int64_t)bh * a.qtiles + qt) * a.nsplit + s) * kQueryTile + wave * kQw + q] = x;
+}
+
+// One workgroup per 32 query rows (a wave's of the main pass), wave n for
+// channels 32 n .. 32 n + 31; lane (q, h) holds what it held in the main pass.
+__global__ __launch_bounds__(256) void split_combine_kernel(AttnArgs a) {
+    const int n = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = lane & 31, h = lane >> 5;
+    const int64_t tile = blockIdx.x >> 2;  // (head, query tile)
+    const int wave = blockIdx.x & 3;
+    const int64_t bh = tile / a.qtiles;
+    const int qi = (int)(tile - bh * a.qtiles) * kQueryTile + wave * kQw + q;
+    const float2* ml = a.part_ml + tile * a.nsplit * kQueryTile + wave * kQw + q;
+    const float4* po = a.part_o + (tile * a.nsplit * kWaves + wave) * 1024 + n * 256 + lane;
+    const float m = ml[(a.nsplit - 1) * kQueryTile].x;  // the running maximum after all keys
+    float l = 0.f;
+    v16f O = {};
+#pragma unroll 2
+    for (int s = 0; s < a.nsplit; s++) {
+        const float2 x = ml[s * kQueryTile];
+        const float w = __builtin_amdgcn_exp2f(x.x - m);
+        l = __builtin_fmaf(w, x.y, l);
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            const float4 o = po[(int64_t)s * kWaves * 1024 + g * 64];
+            O[4 * g] = __builtin_fmaf(w, o.x, O[4 * g]);
+            O[4 * g + 1] = __builtin_fmaf(w, o.y, O[4 * g + 1]);
+            O[4 * g + 2] = __builtin_fmaf(w, o.z, O[4 * g + 2]);
+            O[4 * g + 3] = __builtin_fmaf(w, o.w, O[4 * g + 3]);
+        }
+    }
+    uint32_t w[4][2];
+    pack_channels(O, 1.0f / l, w);
+    if (qi < a.Nq) {
+        uint16_t* dst = a.out + (bh * a.Nq + qi) * 128 + 32 * n + 8 * h;
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+            *reinterpret_cast<uint4*>(dst + 16 * j) =
+                make_uint4(w[2 * j][0], w[2 * j][1], w[2 * j + 1][0], w[2 * j + 1][1]);
+    }
 }
 
 // Short key sequences (cross-attention over a text context, at most
@@ -950,7 +1114,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArg
     const bool staged = ntiles <= kStagedStoreMaxTiles;
     uint8_t* const ostage = lds + ntiles * kStageBytes + wave * kOutStageBytes;
 
-    const TileLoader loader(a, bh, wave, lane);
+    const TileLoader loader(a, bh, 0, wave, lane);
     for (int t = 0; t < ntiles; t++) loader.load(lds + t * kStageBytes, t);
 
     const v8i sel = row_sum_selector(lane);
@@ -1056,30 +1220,65 @@ hipError_t launch_tile_scales(const uint8_t* ks, const uint8_t* vs, uint8_t* out
     return hipGetLastError();
 }
 
+// Dividing pays where the undivided loop leaves the chip idle for longer than
+// the division costs.  In tenths of a microsecond, measured: a tile takes 11
+// with one workgroup per CU, and 17 plus 4 for its scores with two, as the
+// divided passes run (512 workgroups); the score pass, the partial results
+// (33 MB written and read at 512 workgroups) and the combination cost 160.
+// Required is a tenth less than the undivided time.  Runs have at least four
+// tiles: shorter ones cost more in partial results than they gain (70 tiles, 4
+// workgroups: 36 us in 17 runs, 40 in 35).  Both sides of the line (forward,
+// uos_pnq): 64 workgroups x 64 tiles, 8 runs, 79 -> 49 us; 48 x 929, 10 runs,
+// 1290 -> 574; undivided stay 60 x 20 (34.8, divided 37.9) and 160 x 32 (48.0,
+// in 3 runs 54.3); two runs gain nothing at any length (224 x 32: 50 -> 63).
+int key_splits(int64_t BH, int64_t Nq, int64_t Nkv) {
+    const int64_t wgs = BH * ((Nq + kQueryTile - 1) / kQueryTile), tiles = (Nkv + kKvTile - 1) / kKvTile;
+    if (Nkv <= kResidentKeys) return 1;
+    const int64_t slots = kMaxSplitWorkgroups / wgs;
+    const int64_t n = slots < tiles / 4 ? slots : tiles / 4;
+    if (n < 2) return 1;
+    return 10 * (11 * tiles) > 11 * (21 * tiles / n + 160) ? (int)n : 1;
+}
+
+template <bool kQraw, bool kSplit>
+static void launch_pipelined(const AttnArgs& a, int mode, dim3 grid, hipStream_t stream) {
+    switch (mode) {
+        case 0: attention_pipelined_kernel<kRuleOcp, false, kQraw, kSplit><<<grid, kThreads, 0, stream>>>(a); break;
+        case 1: attention_pipelined_kernel<kRuleUos, false, kQraw, kSplit><<<grid, kThreads, 0, stream>>>(a); break;
+        default: attention_pipelined_kernel<kRuleUos, true, kQraw, kSplit><<<grid, kThreads, 0, stream>>>(a); break;
+    }
+}
+
 template <bool kQraw>
-static void launch_attention_q(const AttnArgs& a, int mode, dim3 grid, hipStream_t stream) {
+static hipError_t launch_attention_q(const AttnArgs& a, int mode, dim3 grid, hipStream_t stream) {
     if (a.N <= kResidentKeys) {
         switch (mode) {
             case 0: attention_resident_kernel<kRuleOcp, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
             case 1: attention_resident_kernel<kRuleUos, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
             default: attention_resident_kernel<kRuleUos, true, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
         }
-        return;
+        return hipGetLastError();
     }
-    switch (mode) {
-        case 0: attention_pipelined_kernel<kRuleOcp, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
-        case 1: attention_pipelined_kernel<kRuleUos, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
-        default: attention_pipelined_kernel<kRuleUos, true, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
+    if (a.nsplit <= 1) {
+        launch_pipelined<kQraw, false>(a, mode, grid, stream);
+        return hipGetLastError();
     }
+    const int tiles = a.total_tiles / a.nsplit;  // (head, query tile)
+    const dim3 sgrid((unsigned)(8 * ((tiles * (a.nsplit - 1) + 7) / 8)));
+    if (mode == 0)
+        split_scores_kernel<kRuleOcp, kQraw><<<sgrid, kThreads, 0, stream>>>(a);
+    else
+        split_scores_kernel<kRuleUos, kQraw><<<sgrid, kThreads, 0, stream>>>(a);
+    if (hipError_t e = hipGetLastError()) return e;
+    launch_pipelined<kQraw, true>(a, mode, grid, stream);
+    if (hipError_t e = hipGetLastError()) return e;
+    split_combine_kernel<<<dim3((unsigned)(4 * tiles)), 256, 0, stream>>>(a);
+    return hipGetLastError();
 }
 
 hipError_t launch_attention(const AttnArgs& a, int mode, hipStream_t stream) {
     const dim3 grid((unsigned)(8 * a.per_xcd));
-    if (a.qraw)
-        launch_attention_q<true>(a, mode, grid, stream);
-    else
-        launch_attention_q<false>(a, mode, grid, stream);
-    return hipGetLastError();
+    return a.qraw ? launch_attention_q<true>(a, mode, grid, stream) : launch_attention_q<false>(a, mode, grid, stream);
 }
 
 }  // namespace mxattn

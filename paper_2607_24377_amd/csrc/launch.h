@@ -64,7 +64,21 @@ struct AttnArgs {
     int total_tiles;    // workgroups that do work
     int per_xcd;
     int nchunks;        // resident kernel: workgroups per (batch, head)
+    int nsplit;         // runs the keys of a head are divided into (1: not divided), and their workspace:
+    float* run_max;     // [BH, qtiles, nsplit, 128]: largest score of a run
+    float2* part_ml;    // [BH, qtiles, nsplit, 128]: m and l after a run
+    float4* part_o;     // [BH, qtiles, nsplit, 4 waves, 16, 64 lanes]: O~ of a run
 };
+
+// Runs the keys of a head are divided into, from the shape alone (so every
+// entry point divides alike): see attention.hip.
+int key_splits(int64_t BH, int64_t Nq, int64_t Nkv);
+// Workspace of a divided call: at most kMaxSplitWorkgroups workgroups' worth.
+constexpr int kMaxSplitWorkgroups = 512;
+constexpr size_t kSplitBytesPerWorkgroup = 128 * (128 * 4 + 8 + 4);
+inline size_t split_bytes(int64_t BH, int64_t Nq, int nsplit) {
+    return nsplit <= 1 ? 0 : (size_t)(BH * ((Nq + kQueryTile - 1) / kQueryTile) * nsplit) * kSplitBytesPerWorkgroup;
+}
 
 // Largest key (and value) length of the fused attention kernel: one head's
 // K^ codes (64 B per key) and V^ codes (128 channels x 16 B per 32 keys) are

@@ -101,3 +101,24 @@ def test_resident_staged_stores_several_query_tiles(mx):
     for mode in ("ocp_vanilla", "uos_pnq"):
         _check(mx, w, mode, [0, 9, 15], 40, w.name)
     torch.cuda.empty_cache()
+
+
+# few query tiles over many keys: the keys are divided into runs that several
+# workgroups take (the last case: one tile less than the shortest divided one)
+@pytest.mark.parametrize("B,H,Nq,Nkv", [(1, 1, 130, 3073), (2, 2, 37, 8951), (1, 3, 300, 6400),
+                                        (1, 5, 1280, 9000), (1, 1, 130, 3072)])
+def test_divided_keys(mx, B, H, Nq, Nkv):
+    w = inputs.Workload(73, f"divided_{B}x{H}x{Nq}x{Nkv}", B, H, Nq, 128, "cross", Nkv=Nkv)
+    for mode in MODES:
+        _check(mx, w, mode, [0, B * H - 1], 40, w.name)
+    # the entry point that allocates nothing divides alike
+    qt, kt, vt = (mx.bf16_from_bits(x) for x in inputs.generate(w))
+    qc, qs = mx.quantize(qt, mx.AXIS_HEAD_DIM, "uos")
+    kc, ks = mx.quantize(kt, mx.AXIS_HEAD_DIM, "uos")
+    vc, vs = mx.quantize(vt, mx.AXIS_TOKENS, "uos")
+    want = mx.cross_attend(qc, qs, kc, ks, vc, vs, Nq, Nkv, "uos")
+    got = torch.full_like(want, float("nan"))
+    st = mx.lib().mxattn_cross_attend_noalloc(*(t.data_ptr() for t in (qc, qs, kc, ks, vc, vs)), got.data_ptr(),
+                                              B, H, Nq, Nkv, 128, 1, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
