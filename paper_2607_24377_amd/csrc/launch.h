@@ -108,7 +108,7 @@ struct SoftmaxRowsArgs {
     float gamma;        // pre-scale (diagnostics)
     double g;           // fp64(1 / gamma)
     double* stats;      // [BH, Nq, 8] (diagnostics)
-    int qtiles;         // set by the launcher
+    int qtiles, runs;   // set by the launcher: row tiles, runs of key tiles
     float c;            // set by the launcher: log2(e) / sqrt(128)
 };
 hipError_t launch_attn_rows(const SoftmaxRowsArgs& a, int64_t BH, int out, hipStream_t stream);

@@ -11,9 +11,9 @@
 //                       first for each row's maximum and normalizer, the
 //                       second forming p = 2^(t - m) / L in fp32 and either
 //                       storing it (a materialized tile of P) or quantizing it
-//                       in 32-key blocks in registers and accumulating the
-//                       row statistics below, so that whole tensors are
-//                       diagnosed without writing P;
+//                       in 32-key blocks in registers (a lane holds a whole
+//                       block) and accumulating the row statistics below, so
+//                       that whole tensors are diagnosed without writing P;
 //   rowsum_diag_kernel  the statistics of a given fp32 P: each row quantized
 //                       in 32-entry blocks (optionally pre-scaled by gamma),
 //                       reduced to the quantized mass, the unquantized mass,
@@ -21,11 +21,26 @@
 //                       saturated, rounded-down, rounded-up and exact
 //                       entries, and the entropy -sum p ln p.
 //
-// Both quantize with the same per-entry arithmetic (diag_add), so on the same
-// p they classify every entry identically and their fp64 sums differ only in
-// the order of additions.  rowsum_diag_kernel is HBM-bound (4 bytes of P per
-// entry read once); attn_rows_kernel in its diagnostic form reads only Q and
-// K and is bound by the two score passes and the per-entry VALU work.
+// Both quantize and sum with the same arithmetic per block (BlockDiag), so on
+// the same p they classify every entry identically and their fp64 sums differ
+// only in the order of additions.
+//
+// Row sums.  m and L of a row are formed in runs of kRunTiles key tiles
+// (RowMax: an online maximum and sum per lane, the two lanes of a row merged
+// at the end of the run) that are merged in key order.  A launch with many row
+// tiles walks the runs in one workgroup per row tile (attn_rows_kernel); one
+// with few, which would leave most of the chip idle, gives every run its own
+// workgroup in two passes with a merge between them (rows_partial_kernel,
+// rows_merge_kernel, rows_write_kernel).  Both form m, L and p from the same
+// operations in the same order, bit for bit.
+//
+// What bounds them (one MI355X): the fused diagnostic vector issue (89 % busy;
+// about 30 vector instructions per entry over the two passes: 40 heads x 4096^2
+// entries in 0.72 ms; with every class summed per entry in fp64 behind compares
+// and selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries HBM
+// (K read twice, P written: 0.08 + 0.25 ms; with one workgroup per row tile
+// 2.9 ms, 40 workgroups on 256 CUs) and their diagnostic again vector issue
+// (0.20 ms = 3.3 TB/s of P; before 0.24 ms).
 #include <cmath>
 
 #include "device_common.h"
@@ -37,73 +52,169 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kRowsPerWg = 128;   // query rows per softmax workgroup (4 waves x 32)
-constexpr int kKeyTile = 128;     // keys staged in LDS per step
-constexpr int kLdsRow = 272;      // bytes per staged key row (256 + 16 of padding)
+constexpr int kRowsPerWg = 128;  // query rows per workgroup (4 waves x 32)
+constexpr int kKeyTile = 128;    // keys staged in LDS per step (32 KiB)
+constexpr int kRunTiles = 8;     // key tiles per run
 constexpr float kNegBig = -3.0e38f;
 
-// Stage keys [tile * 128, tile * 128 + 128) of one head into LDS (zeros past Nkv).
-__device__ __forceinline__ void stage_keys(uint8_t* lds, const uint4* kh, int tile, int Nkv) {
-#pragma unroll
-    for (int it = 0; it < 8; it++) {
-        const int c = threadIdx.x + 256 * it;  // 16-byte chunk of the tile
-        const int key = c >> 4, part = c & 15;
-        const int gk = tile * kKeyTile + key;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (gk < Nkv) v = kh[(int64_t)gk * 16 + part];
-        *reinterpret_cast<uint4*>(lds + key * kLdsRow + part * 16) = v;
-    }
-}
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// S^T for 32 keys (sub-tile j of the staged tile, as A rows) x 32 queries
-// (this wave's, as B columns): lane (col, h) supplies key 32 j + col and query
-// col, each with channels 16 s + 8 h .. + 7 per 16-channel step s.
+// Copies keys [tile * 128, tile * 128 + 128) of one head straight into LDS
+// (buffer loads to LDS; the buffer's range check reads zeros past Nkv).  LDS
+// row 64 c + 32 j + r holds key 64 c + 32 ((r >> 2) & 1) + 16 j + 4 (r >> 3) +
+// (r & 3), so that lane (query, h) finds keys 32 h .. 32 h + 31 of the chunk c
+// in the accumulators of its two score products; the 16-byte slot of a row is
+// XOR-ed with the row, so 16 consecutive rows read at one slot hit 16 bank
+// groups.
+struct KeyStage {
+    const uint8_t* kh;
+    int Nkv, wave;
+    uint32_t off;  // lane offset of the wave's first row
+
+    __device__ __forceinline__ KeyStage(const uint16_t* k, int64_t bh, int nkv, int wave_, int lane)
+        : kh(reinterpret_cast<const uint8_t*>(k) + bh * (int64_t)nkv * 256), Nkv(nkv), wave(wave_) {
+        const int x = lane >> 4;  // row of a load's four
+        off = (uint32_t)((64 * (wave >> 1) + 16 * (wave & 1) + x) * 256 + ((lane & 15) ^ x) * 16);
+    }
+
+    // wave w copies LDS rows 32 w .. 32 w + 31 (A-rows of product (c, j) = (w >> 1, w & 1)), four per
+    // load: row 4 i + x is key 32 (i & 1) + 4 (i >> 1) + x further on, its slots XOR-ed by 4 (i & 3) + x
+    __device__ __forceinline__ void load(uint8_t* lds, int tile_) const {
+        const int tile = __builtin_amdgcn_readfirstlane(tile_);
+        const int64_t left = ((int64_t)Nkv - (int64_t)tile * kKeyTile) * 256;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(kh + (int64_t)tile * kKeyTile * 256), 0, (int)(left < kKeyTile * 256 ? left : kKeyTile * 256),
+            0x00020000);
+        uint32_t base = off;
+        asm volatile("" : "+v"(base));  // the eight offsets are formed here, not kept in registers
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (lds_ptr_t)(lds + wave * 8192 + i * 1024), 16,
+                (int)((base ^ (64 * (i & 3))) + (32 * (i & 1) + 4 * (i >> 1)) * 256), 0, 0, 0);
+    }
+};
+
+// S^T of LDS rows 32 j .. 32 j + 31 (as A rows) x this wave's 32 queries (as B
+// columns): lane (col, h) supplies row 32 j + col and query col, each with
+// channels 16 s + 8 h .. + 7 per 16-channel step s.
 __device__ __forceinline__ v16f scores_t(const bf16x8* qb, const uint8_t* lds, int j, int col, int h) {
     v16f acc;
 #pragma unroll
     for (int i = 0; i < 16; i++) acc[i] = 0.f;
-    const uint8_t* row = lds + (32 * j + col) * kLdsRow + 16 * h;
+    const uint8_t* row = lds + (32 * j + col) * 256;
 #pragma unroll
     for (int s = 0; s < 8; s++) {
-        const bf16x8 ka = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + 32 * s));
+        const bf16x8 ka =
+            __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + (((2 * s + h) ^ (col & 15)) * 16)));
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[s], acc, 0, 0, 0);
     }
     return acc;
 }
 
-// Accumulator i of lane (col, h) holds the score of query col with key
-// (A row) 8 (i / 4) + 4 h + (i % 4) of the 32-key sub-tile: a lane holds 16
-// of the 32 keys of its query, its partner lane col + 32 (1 - 2h) the rest.
-__device__ __forceinline__ int acc_key(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
-
-// log2 of a positive fp32, subnormals included (the hardware logarithm takes
-// them as zero): a subnormal is scaled by 2^32 into the normal range first.
-__device__ __forceinline__ float log2_full(float p) {
-    return p < 1.17549435e-38f ? __builtin_amdgcn_logf(p * 4294967296.0f) - 32.0f : __builtin_amdgcn_logf(p);
+// The scores of the staged tile: sv[c][j][i] is the lane's key 64 c + 32 h +
+// 16 j + i, -inf past the end of the sequence.
+typedef v16f TileScores[2][2];
+__device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds, int t, int Nkv, int col, int h,
+                                            TileScores& sv) {
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) sv[c][j] = scores_t(qb, lds, 2 * c + j, col, h);
+    if ((t + 1) * kKeyTile > Nkv) {
+        const int valid = Nkv - t * kKeyTile - 32 * h;
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int i = 0; i < 16; i++)
+                    if (64 * c + 16 * j + i >= valid) sv[c][j][i] = -INFINITY;
+    }
 }
 
-// Adds one entry's terms to the row statistics (see mxattn.h): p the
-// probability, xs = gamma p / sigma (exact), r its E2M1 value from the
-// 4-bit code, sig = sigma in fp64, g = fp64(1 / gamma).
-__device__ __forceinline__ void diag_add(double* st, float p, float xs, float r, uint32_t code,
-                                         double sig, double g) {
-    const double pd = (double)p;
-    const double qv = (double)r * sig * g;
-    const double cj = qv - pd;
-    const bool zer = p > 0.f && (code & 7u) == 0u;
-    const bool sat = !zer && xs > 6.0f;
-    const bool dn = !zer && !sat && r < xs;
-    const bool up = !zer && !sat && r > xs;
-    const bool ex = !zer && !sat && !dn && !up;
-    st[0] += qv;
-    st[1] += pd;
-    st[2] += zer ? cj : 0.0;
-    st[3] += sat ? cj : 0.0;
-    st[4] += dn ? cj : 0.0;
-    st[5] += up ? cj : 0.0;
-    st[6] += ex ? cj : 0.0;
-    st[7] += p > 0.f ? (double)(p * log2_full(p)) : 0.0;  // p log2 p; scaled by -ln 2 at the end
+// Calls work(t, scores, landed) for the tiles t0 .. t1 - 1.  The next tile is
+// copied into LDS while the work runs on this one's scores, which by then are
+// in registers; the work calls landed() once, where the copy should be through
+// (vmcnt counts stores too: before its stores, so that they are not waited for
+// at the next tile).
+template <typename Work>
+__device__ __forceinline__ void for_tiles(const bf16x8* qb, const KeyStage& ks, uint8_t* lds, int t0, int t1, int col,
+                                          int h, const Work& work) {
+    auto landed = [] { __builtin_amdgcn_s_waitcnt(0); };
+    ks.load(lds, t0);
+    landed();
+    for (int t = t0; t < t1; t++) {
+        __syncthreads();  // tile t landed everywhere
+        TileScores sv;
+        tile_scores(qb, lds, t, ks.Nkv, col, h, sv);
+        __syncthreads();  // and was read everywhere
+        if (t + 1 < t1) ks.load(lds, t + 1);
+        work(t, sv, landed);
+    }
 }
+
+// Query operand (B columns) of local query row lr (clamped to the last row).
+__device__ __forceinline__ void load_queries(const SoftmaxRowsArgs& a, int64_t bh, int lr, int h, bf16x8 (&qb)[8]) {
+    const uint4* qrow = reinterpret_cast<const uint4*>(a.q) + (bh * a.Nq + a.row0 + min(lr, a.rows - 1)) * 16;
+#pragma unroll
+    for (int s = 0; s < 8; s++) qb[s] = __builtin_bit_cast(bf16x8, qrow[2 * s + h]);
+}
+
+// Scores are never NaN: the NaN-propagating maximum fuses into the 3-input form.
+__device__ __forceinline__ float max2f(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
+// Maximum and sum of a row's 2^(t - m), t = c s: (m, l) of a run, or of the
+// runs so far.
+struct RowMax {
+    float m, l;
+};
+__device__ __forceinline__ RowMax merge(RowMax a, RowMax b) {
+    const float m = max2f(a.m, b.m);
+    const float bl = b.l * __builtin_amdgcn_exp2f(b.m - m);
+    return {m, __builtin_fmaf(a.l, __builtin_amdgcn_exp2f(a.m - m), bl)};
+}
+
+// (m, l) of the row over tiles t0 .. t1 - 1 (t0 at the start of a run), the
+// same in both of the row's lanes.
+__device__ __forceinline__ RowMax row_max(const SoftmaxRowsArgs& a, const KeyStage& ks, const bf16x8* qb, uint8_t* lds,
+                                          int t0, int t1, int col, int h) {
+    RowMax total = {kNegBig, 0.f}, r = total;
+    for_tiles(qb, ks, lds, t0, t1, col, h, [&](int t, TileScores& sv, auto landed) {
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            float x = sv[c][0][0], y = sv[c][1][0];
+#pragma unroll
+            for (int i = 1; i < 15; i += 2) {
+                x = max2f(max2f(x, sv[c][0][i]), sv[c][0][i + 1]);
+                y = max2f(max2f(y, sv[c][1][i]), sv[c][1][i + 1]);
+            }
+            // (a lane whose 32 keys are all past the end keeps m: c x = -inf)
+            const float mn = max2f(r.m, a.c * max2f(max2f(x, sv[c][0][15]), max2f(y, sv[c][1][15])));
+            float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][0][i], a.c, -mn));
+                s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][1][i], a.c, -mn));
+            }
+            r.l = __builtin_fmaf(r.l, __builtin_amdgcn_exp2f(r.m - mn), s0 + s1);
+            r.m = mn;
+        }
+        if ((t + 1) % kRunTiles == 0 || t + 1 == t1) {  // the run's end
+            const RowMax o = {__shfl_xor(r.m, 32), __shfl_xor(r.l, 32)};
+            r = h == 0 ? merge(r, o) : merge(o, r);
+            total = t < t0 + kRunTiles ? r : merge(total, r);
+            r = {kNegBig, 0.f};
+        }
+        landed();
+    });
+    return total;
+}
+
+// log2 of a positive fp32; what is below the normal range counts as 2^-126
+// (the hardware logarithm takes it as zero), which changes p log2 p by less
+// than 2^-125.  Zero gives a finite value, so p log2 p is 0 for p = 0.
+__device__ __forceinline__ float log2_full(float p) { return __builtin_amdgcn_logf(fmaxf(p, 1.17549435e-38f)); }
 
 // Shared-scale exponent of a block from the bits of its largest magnitude.
 template <int kRule>
@@ -111,214 +222,432 @@ __device__ __forceinline__ int block_exponent_f32(uint32_t mb) {
     return mb == 0 ? 0 : scale_exponent_f32<kRule>(mb);
 }
 
-// Rows of attention probabilities: S^T on the bf16 matrix cores, pass 1 the
-// row maximum m and normalizer L of t = s c, pass 2 p = 2^(t - m) / L, then
-// kOut = 0: p stored as fp32 rows; kOut = 1 (UOS) or 2 (OCP): p quantized in
-// 32-key blocks in registers and the row statistics of rowsum_diag_kernel
-// accumulated, so the diagnostic of a whole tensor never materializes P.
-template <int kOut>
-__global__ __launch_bounds__(256) void attn_rows_kernel(SoftmaxRowsArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * kLdsRow];
-    const int bh = blockIdx.x / a.qtiles, qt = blockIdx.x % a.qtiles;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int col = lane & 31, h = lane >> 5;
-    const int lr = qt * kRowsPerWg + 32 * wave + col;  // this lane's local query row
-    const bool row_ok = lr < a.rows;
+// fp32 to unsigned, fractions dropped and negatives 0 (the conversion clamps).
+__device__ __forceinline__ uint32_t cvt_u32(float x) {
+    uint32_t r;
+    asm("v_cvt_u32_f32_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+__device__ __forceinline__ uint32_t cvt_u32_neg(float x) {
+    uint32_t r;
+    asm("v_cvt_u32_f32_e64 %0, -%1" : "=v"(r) : "v"(x));
+    return r;
+}
 
-    // Q operand (B columns): query row lr (clamped; only valid rows are written)
-    const int lq = min(lr, a.rows - 1);
-    const uint4* qrow = reinterpret_cast<const uint4*>(a.q) + ((int64_t)bh * a.Nq + a.row0 + lq) * 16;
-    bf16x8 qb[8];
-#pragma unroll
-    for (int s = 0; s < 8; s++) qb[s] = __builtin_bit_cast(bf16x8, qrow[2 * s + h]);
+// Row statistics of a lane, added up block by block (see mxattn.h).
+//
+// kGamma = kGammaOne, kGammaPow2: gamma is 1, the usual one, or a power of two
+// up to 2^16, so that x = gamma p is exact.  Then an entry's contribution is (r - x / sigma) sigma /
+// gamma exactly, r its E2M1 value, and with r > 0 (so x / sigma >= 1/4) the
+// difference is a multiple of 2^-25 of at most 2: the up, down and saturated
+// entries of a block add up exactly in 32-bit integers (at most 32 * 2 * 2^25),
+// one fp64 product and sum per block each; only zeroed entries and the entropy
+// take an fp64 sum per entry.  Otherwise every entry's terms are formed and
+// added in fp64.
+enum Gamma { kGammaOne = 0, kGammaPow2 = 1, kGammaAny = 2 };
+template <int kGamma>
+struct RowStats {
+    static constexpr bool kPow2 = kGamma != kGammaAny;
+    // kPow2: sum Q, up, down, saturated (the last two positive), zeroed p, p log2 p;
+    // otherwise the eight statistics, the last as sum p log2 p
+    static constexpr int kSums = kPow2 ? 6 : 8;
+    double v[kSums];
+};
 
-    const uint4* kh = reinterpret_cast<const uint4*>(a.k) + (int64_t)bh * a.Nkv * 16;
-    const int tiles = (a.Nkv + kKeyTile - 1) / kKeyTile;
-
-    // pass 1: running maximum and normalizer of this lane's 16-key shares
-    float m = kNegBig, l = 0.f;
-    for (int t = 0; t < tiles; t++) {
-        __syncthreads();
-        stage_keys(lds, kh, t, a.Nkv);
-        __syncthreads();
-        v16f sv[4];
+// Adds this lane's kN entries of a block whose largest x has the bits mb.
+// (x is formed again from p where it is needed: registers.)
+template <int kRule, int kGamma, int kN>
+__device__ __forceinline__ void add_block(RowStats<kGamma>& st, const float (&p)[kN], float gamma, uint32_t mb,
+                                          double g) {
+    if constexpr (kGamma == kGammaOne) gamma = 1.0f;
+    const int ex = block_exponent_f32<kRule>(mb);
+    const float sf = e8m0_as_f32((uint32_t)(ex + 127));
+    if constexpr (kGamma != kGammaAny) {
+        constexpr float k25 = 33554432.0f;  // 2^25
+        uint32_t up = 0, down = 0, sat = 0;
+        float rsum = 0.f;  // multiples of 2^24 below 2^33: exact
 #pragma unroll
-        for (int j = 0; j < 4; j++) sv[j] = scores_t(qb, lds, j, col, h);
-        float tm = kNegBig;
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const bool valid = t * kKeyTile + 32 * j + acc_key(i, h) < a.Nkv;
-                sv[j][i] = valid ? sv[j][i] * a.c : -INFINITY;
-                tm = fmaxf(tm, sv[j][i]);
+        for (int i = 0; i < kN; i += 2) {
+            // (forms the sums entry by entry, no instruction emitted: with the
+            // work of the whole block interleaved it spills)
+            if (i % 4 == 0) {
+                asm volatile("" : "+v"(up), "+v"(down), "+v"(sat), "+v"(rsum), "+v"(st.v[4]), "+v"(st.v[5]));
+                __builtin_amdgcn_sched_barrier(0);
             }
-        const float mn = fmaxf(m, tm);
-        float acc = l * __builtin_amdgcn_exp2f(m - mn);
+            const float x[2] = {gamma * p[i], gamma * p[i + 1]};
+            const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[0], x[1], sf, 0);
+            const auto r = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, k25, 0);
+            rsum += r[0] + r[1];
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc += __builtin_amdgcn_exp2f(sv[j][i] - mn);
-        m = mn;
-        l = acc;
-    }
-    {  // the two halves of the row
-        const float mo = __shfl_xor(m, 32);
-        const float lo = __shfl_xor(l, 32);
-        const float mn = fmaxf(m, mo);
-        l = l * __builtin_amdgcn_exp2f(m - mn) + lo * __builtin_amdgcn_exp2f(mo - mn);
-        m = mn;
-    }
-    const float inv = 1.0f / l;
-
-    double st[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) st[i] = 0.0;
-
-    // pass 2
-    for (int t = 0; t < tiles; t++) {
-        __syncthreads();
-        stage_keys(lds, kh, t, a.Nkv);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const v16f sv = scores_t(qb, lds, j, col, h);
-            const int key0 = t * kKeyTile + 32 * j;
-            float p[16];
-#pragma unroll
-            for (int i = 0; i < 16; i++)
-                p[i] = key0 + acc_key(i, h) < a.Nkv ? __builtin_amdgcn_exp2f(sv[i] * a.c - m) * inv : 0.f;
-            if constexpr (kOut == 0) {
-                // keys key0 + 8 (i/4) + 4 h + 0..3 as one 16-byte store each
-                if (row_ok) {
-                    float* prow = a.p + ((int64_t)bh * a.rows + lr) * a.ld;
-#pragma unroll
-                    for (int g = 0; g < 4; g++) {
-                        const int key = key0 + 8 * g + 4 * h;
-                        if (key < a.Nkv)
-                            *reinterpret_cast<float4*>(prow + key) =
-                                make_float4(p[4 * g], p[4 * g + 1], p[4 * g + 2], p[4 * g + 3]);
-                    }
-                }
-            } else {
-                constexpr int kRule = kOut == 1 ? kRuleUos : kRuleOcp;
-                float x[16];
-                uint32_t mb = 0;
-#pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    x[i] = a.gamma * p[i];
-                    mb = max(mb, __builtin_bit_cast(uint32_t, x[i]) & 0x7FFFFFFFu);
-                }
-                mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32));  // the block's other 16 keys
-                const int ex = block_exponent_f32<kRule>(mb);
-                const float sf = e8m0_as_f32((uint32_t)(ex + 127));
-                const float invs = __builtin_bit_cast(float, (uint32_t)(127 - ex) << 23);
-                const double sig = __builtin_bit_cast(double, (uint64_t)(ex + 1023) << 52);
-#pragma unroll
-                for (int i = 0; i < 16; i += 2) {
-                    const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[i], x[i + 1], sf, 0);
-                    const auto r = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 0);
-                    diag_add(st, p[i], x[i] * invs, r[0], c & 0xFu, sig, a.g);
-                    diag_add(st, p[i + 1], x[i + 1] * invs, r[1], (c >> 4) & 0xFu, sig, a.g);
-                }
+            for (int e = 0; e < 2; e++) {
+                const float xs = __builtin_ldexpf(x[e], 25 - ex);
+                const float d = r[e] - xs;
+                const bool zero = r[e] == 0.f;
+                up += cvt_u32(d);
+                down += zero ? 0u : cvt_u32_neg(d);
+                sat += cvt_u32(xs - 6.0f * k25);
+                st.v[4] += (double)(zero ? p[i + e] : 0.f);
+                st.v[5] += (double)(p[i + e] * log2_full(p[i + e]));
             }
         }
-    }
-    if constexpr (kOut != 0) {
+        // sigma / gamma 2^-25
+        const double s = __builtin_bit_cast(double, (uint64_t)(ex + 1023 - 25) << 52) * g;
+        st.v[0] += s * (double)rsum;
+        st.v[1] += s * (double)up;
+        st.v[2] += s * (double)(down - sat);
+        st.v[3] += s * (double)sat;
+    } else {
+        const float inv = __builtin_bit_cast(float, (uint32_t)(127 - ex) << 23);  // 2^-ex, normal
+        const double sig = __builtin_bit_cast(double, (uint64_t)(ex + 1023) << 52);
 #pragma unroll
-        for (int i = 0; i < 8; i++) st[i] += __shfl_xor(st[i], 32);
-        st[7] *= -0.6931471805599453;  // -sum p ln p = -ln 2 sum p log2 p
-        if (row_ok && h == 0) {
-            double* dst = a.stats + ((int64_t)bh * a.Nq + a.row0 + lr) * 8;
+        for (int i = 0; i < kN; i += 2) {
+            if (i % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+            const float x[2] = {gamma * p[i], gamma * p[i + 1]};
+            const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[0], x[1], sf, 0);
+            const auto r = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 0);
 #pragma unroll
-            for (int i = 0; i < 8; i++) dst[i] = st[i];
+            for (int e = 0; e < 2; e++) {
+                const float xs = x[e] * inv;  // exact
+                const double pd = (double)p[i + e];
+                const double qv = (double)r[e] * sig * g;
+                const double cj = qv - pd;
+                const bool zer = p[i + e] > 0.f && r[e] == 0.f;
+                const bool sat = !zer && xs > 6.0f;
+                const bool dn = !zer && !sat && r[e] < xs;
+                const bool up = !zer && !sat && r[e] > xs;
+                const bool eq = !zer && !sat && !dn && !up;
+                st.v[0] += qv;
+                st.v[1] += pd;
+                st.v[2] += zer ? cj : 0.0;
+                st.v[3] += sat ? cj : 0.0;
+                st.v[4] += dn ? cj : 0.0;
+                st.v[5] += up ? cj : 0.0;
+                st.v[6] += eq ? cj : 0.0;
+                st.v[7] += (double)(p[i + e] * log2_full(p[i + e]));
+            }
         }
     }
 }
 
-// One workgroup per row; 8 lanes per 32-entry block, 4 entries per lane.
-template <int kRule>
+// The eight statistics of a row from its sums over all lanes.
+template <int kGamma>
+__device__ __forceinline__ void write_stats(double* dst, const RowStats<kGamma>& st) {
+    constexpr double kMinusLn2 = -0.6931471805599453;  // -sum p ln p = -ln 2 sum p log2 p
+    if constexpr (kGamma != kGammaAny) {
+        const double R = st.v[0], up = st.v[1], down = st.v[2], sat = st.v[3], z = st.v[4];
+        dst[0] = R;
+        dst[1] = R + z + ((down + sat) - up);  // the mass: what was quantized less what it gained
+        dst[2] = -z;
+        dst[3] = -sat;
+        dst[4] = -down;
+        dst[5] = up;
+        dst[6] = 0.0;
+        dst[7] = kMinusLn2 * st.v[5];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 7; i++) dst[i] = st.v[i];
+        dst[7] = kMinusLn2 * st.v[7];
+    }
+}
+
+// A wave's place: its 32 query rows of a row tile.
+struct RowPlace {
+    int64_t bh;
+    int qt, wave, lane, col, h, lr;
+    bool ok;
+    __device__ __forceinline__ RowPlace(const SoftmaxRowsArgs& a, int64_t tile) {
+        bh = tile / a.qtiles;
+        qt = (int)(tile - bh * a.qtiles);
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        lane = threadIdx.x & 63;
+        col = lane & 31;
+        h = lane >> 5;
+        lr = qt * kRowsPerWg + 32 * wave + col;  // this lane's local query row
+        ok = lr < a.rows;
+    }
+    __device__ __forceinline__ float* prow(const SoftmaxRowsArgs& a) const {
+        return a.p + (bh * a.rows + lr) * (int64_t)a.ld;
+    }
+};
+
+// p of the staged tile's entries: stored (kOut = kRowsStoreP) or diagnosed.
+// A lane holds 32 consecutive entries of one row, so stored straight from
+// registers every store instruction would touch 64 cache lines 16 bytes each
+// (2.2 TB/s written); 16 rows x 64 entries at a time go through the wave's
+// 4 KiB of `out` (slots of a row XOR-ed by the row) and leave as four 256-byte
+// row pieces per instruction.
+constexpr int kOutBytes = 4096;  // per wave
+template <int kOut, int kGamma, typename Landed>
+__device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPlace& w, TileScores& sv, uint8_t* out,
+                                          int t, float m, float inv, RowStats<kGamma>& st, const Landed& landed) {
+    if constexpr (kOut == kRowsStoreP) {
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int i = 0; i < 16; i++)
+                    sv[c][j][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][j][i], a.c, -m)) * inv;
+        landed();
+        const int row0 = w.qt * kRowsPerWg + 32 * w.wave;
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int pass = 0; pass < 2; pass++) {
+                if ((w.col >> 4) == pass) {
+                    const int row = w.col & 15;
+#pragma unroll
+                    for (int n = 0; n < 32; n += 4) {
+                        const v16f& p = sv[c][n >> 4];
+                        *reinterpret_cast<float4*>(out + row * 256 + (((8 * w.h + n / 4) ^ row) * 16)) =
+                            make_float4(p[n & 15], p[(n & 15) + 1], p[(n & 15) + 2], p[(n & 15) + 3]);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const int row = 4 * k + (w.lane >> 4), slot = w.lane & 15;
+                    const float4 v = *reinterpret_cast<const float4*>(out + row * 256 + ((slot ^ row) * 16));
+                    const int r = row0 + 16 * pass + row, key = t * kKeyTile + 64 * c + 4 * slot;
+                    if (r < a.rows && key < a.Nkv)
+                        *reinterpret_cast<float4*>(a.p + (w.bh * a.rows + r) * (int64_t)a.ld + key) = v;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+    } else {
+        constexpr int kRule = kOut == kRowsDiagUos ? kRuleUos : kRuleOcp;
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            float p[32], mx = 0.f;  // gamma > 0: the largest x is gamma times the largest p
+#pragma unroll
+            for (int n = 0; n < 32; n++)
+                p[n] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][n >> 4][n & 15], a.c, -m)) * inv;
+#pragma unroll
+            for (int n = 0; n < 32; n += 2) mx = max2f(max2f(mx, p[n]), p[n + 1]);
+            add_block<kRule, kGamma, 32>(st, p, a.gamma, __builtin_bit_cast(uint32_t, a.gamma * mx), a.g);
+        }
+        landed();
+    }
+}
+
+// Rows of attention probabilities, one workgroup per 128 query rows: pass 1
+// the row maximum m and normalizer L run by run, pass 2 p.
+template <int kOut, int kGamma>
+__global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
+    __shared__ __attribute__((aligned(16))) uint8_t out[kOut == kRowsStoreP ? 4 * kOutBytes : 16];
+    const RowPlace w(a, blockIdx.x);
+    bf16x8 qb[8];
+    load_queries(a, w.bh, w.lr, w.h, qb);
+    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    const int tiles = (a.Nkv + kKeyTile - 1) / kKeyTile;
+
+    const RowMax r = row_max(a, ks, qb, lds, 0, tiles, w.col, w.h);
+    const float inv = 1.0f / r.l;
+
+    RowStats<kGamma> st;
+#pragma unroll
+    for (int i = 0; i < RowStats<kGamma>::kSums; i++) st.v[i] = 0.0;
+    for_tiles(qb, ks, lds, 0, tiles, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
+        emit_tile<kOut, kGamma>(a, w, sv, out + (kOut == kRowsStoreP ? w.wave * kOutBytes : 0), t, r.m, inv, st,
+                                landed);
+    });
+    if constexpr (kOut != kRowsStoreP) {
+#pragma unroll
+        for (int i = 0; i < RowStats<kGamma>::kSums; i++) st.v[i] += __shfl_xor(st.v[i], 32);
+        if (w.ok && w.h == 0) write_stats(a.stats + (w.bh * a.Nq + a.row0 + w.lr) * 8, st);
+    }
+}
+
+// Few row tiles: one workgroup per (row tile, run).  The run's (m, l) goes to
+// the first two of the run's own entries of the row (p has room for at least
+// four there), where rows_merge_kernel leaves the row's m and 1 / L for every
+// run; a workgroup of rows_write_kernel reads that pair of its own run before
+// it overwrites it, so no other workspace is needed.
+__global__ __launch_bounds__(256, 3) void rows_partial_kernel(SoftmaxRowsArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
+    const RowPlace w(a, blockIdx.x / a.runs);
+    const int run = blockIdx.x % a.runs;
+    bf16x8 qb[8];
+    load_queries(a, w.bh, w.lr, w.h, qb);
+    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    const int t1 = min((a.Nkv + kKeyTile - 1) / kKeyTile, (run + 1) * kRunTiles);
+    const RowMax r = row_max(a, ks, qb, lds, run * kRunTiles, t1, w.col, w.h);
+    if (w.ok && w.h == 0) *reinterpret_cast<float2*>(w.prow(a) + run * (kRunTiles * kKeyTile)) = make_float2(r.m, r.l);
+}
+
+// One wave per row: its lanes read 64 runs' pairs at once, which every lane
+// then merges in order.
+__global__ __launch_bounds__(256) void rows_merge_kernel(SoftmaxRowsArgs a, int64_t rows) {
+    const int64_t i = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (i >= rows) return;
+    const int lane = threadIdx.x & 63;
+    float* row = a.p + i * a.ld;
+    constexpr int kStep = kRunTiles * kKeyTile;
+    RowMax r = {kNegBig, 0.f};
+    for (int run0 = 0; run0 < a.runs; run0 += 64) {
+        const float2 x = *reinterpret_cast<const float2*>(row + (int64_t)min(run0 + lane, a.runs - 1) * kStep);
+        const int n = min(64, a.runs - run0);
+        for (int e = 0; e < n; e++) {
+            const RowMax y = {__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.x), e)),
+                              __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.y), e))};
+            r = run0 + e == 0 ? y : merge(r, y);
+        }
+    }
+    const float inv = 1.0f / r.l;
+    for (int run = lane; run < a.runs; run += 64)
+        *reinterpret_cast<float2*>(row + (int64_t)run * kStep) = make_float2(r.m, inv);
+}
+
+__global__ __launch_bounds__(256, 3) void rows_write_kernel(SoftmaxRowsArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
+    __shared__ __attribute__((aligned(16))) uint8_t out[4 * kOutBytes];
+    const RowPlace w(a, blockIdx.x / a.runs);
+    const int run = blockIdx.x % a.runs;
+    bf16x8 qb[8];
+    load_queries(a, w.bh, w.lr, w.h, qb);
+    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    float2 mi = make_float2(0.f, 0.f);
+    if (w.ok) mi = *reinterpret_cast<const float2*>(w.prow(a) + run * (kRunTiles * kKeyTile));
+    RowStats<kGammaOne> st;
+    const int t1 = min((a.Nkv + kKeyTile - 1) / kKeyTile, (run + 1) * kRunTiles);
+    // (the wait for the first tile is also one for the pair)
+    for_tiles(qb, ks, lds, run * kRunTiles, t1, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
+        emit_tile<kRowsStoreP, kGammaOne>(a, w, sv, out + w.wave * kOutBytes, t, mi.x, mi.y, st, landed);
+    });
+}
+
+// One workgroup per row; 4 lanes per 32-entry block, 8 entries per lane.
+template <int kRule, int kGamma>
 __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
-    __shared__ double red[4][8];
+    constexpr int kSums = RowStats<kGamma>::kSums;
+    __shared__ double red[4][kSums];
     const int64_t r = blockIdx.x;
     const float* prow = a.p + r * a.ld;
-    double st[8];
+    RowStats<kGamma> st;
 #pragma unroll
-    for (int i = 0; i < 8; i++) st[i] = 0.0;
+    for (int i = 0; i < kSums; i++) st.v[i] = 0.0;
+    const float gamma = kGamma == kGammaOne ? 1.0f : a.gamma;
 
-    for (int64_t base = 0; base < a.N; base += 1024) {
-        const int64_t j = base + 4 * threadIdx.x;  // 4 entries of block j / 32
-        float p[4] = {0.f, 0.f, 0.f, 0.f};
-        if (j < a.N) {
-            const float4 v = *reinterpret_cast<const float4*>(prow + j);
-            p[0] = v.x;
-            p[1] = j + 1 < a.N ? v.y : 0.f;
-            p[2] = j + 2 < a.N ? v.z : 0.f;
-            p[3] = j + 3 < a.N ? v.w : 0.f;
-        }
-        float x[4];
-        uint32_t mb = 0;
+    auto block = [&](const float (&p)[8]) {
+        float mx = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            x[e] = a.gamma * p[e];
-            mb = max(mb, __builtin_bit_cast(uint32_t, x[e]) & 0x7FFFFFFFu);
-        }
-        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 1));
-        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 2));
-        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 4));
-        const int ex = block_exponent_f32<kRule>(mb);
-        const float sf = e8m0_as_f32((uint32_t)(ex + 127));
-        const float inv = __builtin_bit_cast(float, (uint32_t)(127 - ex) << 23);  // 2^-ex, normal
-        const double sig = __builtin_bit_cast(double, (uint64_t)(ex + 1023) << 52);
-        uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[0], x[1], sf, 0);
-        c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, x[2], x[3], sf, 1);
-        const auto r01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 0);
-        const auto r23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 1);
-        const float rq[4] = {r01[0], r01[1], r23[0], r23[1]};
-#pragma unroll
-        for (int e = 0; e < 4; e++) diag_add(st, p[e], x[e] * inv, rq[e], (c >> (4 * e)) & 0xFu, sig, a.g);
+        for (int e = 0; e < 8; e += 2)
+            mx = max2f(max2f(mx, __builtin_fabsf(gamma * p[e])), __builtin_fabsf(gamma * p[e + 1]));
+        uint32_t mb = __builtin_bit_cast(uint32_t, mx);
+        mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0xB1, 0xF, 0xF, false));  // lane ^ 1
+        mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0x4E, 0xF, 0xF, false));  // lane ^ 2
+        add_block<kRule, kGamma, 8>(st, p, a.gamma, mb, a.g);
+    };
+    // entries 8 t .. 8 t + 7 of each whole step of 2048, the next step's
+    // fetched before a step is worked on
+    const int64_t whole = a.N / 2048 * 2048;
+    const float4* src = reinterpret_cast<const float4*>(prow) + 2 * threadIdx.x;
+    float4 n0 = make_float4(0.f, 0.f, 0.f, 0.f), n1 = n0;
+    if (whole > 0) {
+        n0 = src[0];
+        n1 = src[1];
     }
-    // -sum p ln p = -ln 2 * sum p log2 p
-    st[7] *= -0.6931471805599453;
+    for (int64_t base = 0; base < whole; base += 2048) {
+        const float p[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+        const int64_t nb = base + 2048 < whole ? base + 2048 : base;  // the last step reads itself again
+        n0 = src[nb / 4];
+        n1 = src[nb / 4 + 1];
+        block(p);
+    }
+    if (whole < a.N) {  // the rest of the row, zeros past its end
+        const int64_t j = whole + 8 * threadIdx.x;
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j + e < a.N) v = *reinterpret_cast<const float4*>(prow + j + e);  // ld % 4 == 0
+            p[e] = v.x;
+            p[e + 1] = j + e + 1 < a.N ? v.y : 0.f;
+            p[e + 2] = j + e + 2 < a.N ? v.z : 0.f;
+            p[e + 3] = j + e + 3 < a.N ? v.w : 0.f;
+        }
+        block(p);
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-        for (int i = 0; i < 8; i++) st[i] += __shfl_xor(st[i], off);
+        for (int i = 0; i < kSums; i++) st.v[i] += __shfl_xor(st.v[i], off);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
-        for (int i = 0; i < 8; i++) red[wave][i] = st[i];
+        for (int i = 0; i < kSums; i++) red[wave][i] = st.v[i];
     __syncthreads();
-    if (threadIdx.x < 8) {
-        const int i = threadIdx.x;
-        const double v = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < kSums; i++) st.v[i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
         const int64_t head = r / a.rows_per_head, lr = r % a.rows_per_head;
-        a.stats[((head * a.out_rows_per_head) + a.out_row0 + lr) * 8 + i] = v;
+        write_stats(a.stats + ((head * a.out_rows_per_head) + a.out_row0 + lr) * 8, st);
     }
 }
 
+// The arithmetic that gamma allows (RowStats).
+int gamma_kind(float gamma) {
+    int e;
+    if (gamma == 1.0f) return kGammaOne;
+    return gamma > 1.0f && gamma <= 65536.0f && std::frexp(gamma, &e) == 0.5f ? kGammaPow2 : kGammaAny;
+}
+
 }  // namespace
+
+template <int kGamma>
+static void launch_attn_diag(const SoftmaxRowsArgs& a, int out, dim3 grid, hipStream_t stream) {
+    if (out == kRowsDiagUos)
+        attn_rows_kernel<kRowsDiagUos, kGamma><<<grid, 256, 0, stream>>>(a);
+    else
+        attn_rows_kernel<kRowsDiagOcp, kGamma><<<grid, 256, 0, stream>>>(a);
+}
 
 hipError_t launch_attn_rows(const SoftmaxRowsArgs& args, int64_t BH, int out, hipStream_t stream) {
     SoftmaxRowsArgs a = args;
     a.qtiles = (a.rows + kRowsPerWg - 1) / kRowsPerWg;
     a.c = 0.12751743082459868f;  // fp32(log2(e) / sqrt(128))
-    const dim3 grid((unsigned)(BH * a.qtiles));
-    if (out == kRowsStoreP)
-        attn_rows_kernel<0><<<grid, 256, 0, stream>>>(a);
-    else if (out == kRowsDiagUos)
-        attn_rows_kernel<1><<<grid, 256, 0, stream>>>(a);
-    else
-        attn_rows_kernel<2><<<grid, 256, 0, stream>>>(a);
+    a.runs = (a.Nkv + kRunTiles * kKeyTile - 1) / (kRunTiles * kKeyTile);
+    const int64_t tiles = BH * a.qtiles;
+    if (out != kRowsStoreP) {
+        switch (gamma_kind(a.gamma)) {
+            case kGammaOne: launch_attn_diag<kGammaOne>(a, out, dim3((unsigned)tiles), stream); break;
+            case kGammaPow2: launch_attn_diag<kGammaPow2>(a, out, dim3((unsigned)tiles), stream); break;
+            default: launch_attn_diag<kGammaAny>(a, out, dim3((unsigned)tiles), stream); break;
+        }
+        return hipGetLastError();
+    }
+    // 768 workgroups (three per CU) fill the chip: with fewer row tiles each
+    // run of keys gets a workgroup of its own
+    if (a.runs < 2 || tiles >= 768) {
+        attn_rows_kernel<kRowsStoreP, kGammaOne><<<dim3((unsigned)tiles), 256, 0, stream>>>(a);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)(tiles * a.runs));
+    rows_partial_kernel<<<grid, 256, 0, stream>>>(a);
+    if (hipError_t e = hipGetLastError()) return e;
+    const int64_t rows = BH * a.rows;
+    rows_merge_kernel<<<dim3((unsigned)((rows + 3) / 4)), 256, 0, stream>>>(a, rows);
+    if (hipError_t e = hipGetLastError()) return e;
+    rows_write_kernel<<<grid, 256, 0, stream>>>(a);
     return hipGetLastError();
+}
+
+template <int kGamma>
+static void launch_diag(const RowsumDiagArgs& a, int64_t rows, int rule, hipStream_t stream) {
+    if (rule == kRuleUos)
+        rowsum_diag_kernel<kRuleUos, kGamma><<<dim3((unsigned)rows), 256, 0, stream>>>(a);
+    else
+        rowsum_diag_kernel<kRuleOcp, kGamma><<<dim3((unsigned)rows), 256, 0, stream>>>(a);
 }
 
 hipError_t launch_rowsum_diag(const RowsumDiagArgs& a, int64_t rows, int rule, hipStream_t stream) {
     if (rows == 0) return hipSuccess;
-    if (rule == kRuleUos)
-        rowsum_diag_kernel<kRuleUos><<<dim3((unsigned)rows), 256, 0, stream>>>(a);
-    else
-        rowsum_diag_kernel<kRuleOcp><<<dim3((unsigned)rows), 256, 0, stream>>>(a);
+    switch (gamma_kind(a.gamma)) {
+        case kGammaOne: launch_diag<kGammaOne>(a, rows, rule, stream); break;
+        case kGammaPow2: launch_diag<kGammaPow2>(a, rows, rule, stream); break;
+        default: launch_diag<kGammaAny>(a, rows, rule, stream); break;
+    }
     return hipGetLastError();
 }
 

@@ -173,6 +173,49 @@ def test_fused_diag_cross_lengths(mx):
     _same_stats(fused, two, "Nq=130 Nkv=697")
 
 
+@pytest.mark.parametrize("nkv", [1023, 1025, 2049, 2500])
+def test_runs_of_keys_agree_between_the_paths(mx, nkv):
+    """Keys in runs of 1024: a launch of few rows gives each run a workgroup,
+    one of many rows (and the fused diagnostic) walks the runs in one; rows,
+    statistics and the oracle's softmax agree on both sides of the run edges,
+    the rows bit for bit."""
+    w = inputs.custom(1, 96, max(1024, nkv), kind="video", index=34)
+    q, k, _ = inputs.generate(w)
+    qt = mx.bf16_from_bits(np.ascontiguousarray(q[:, :, :1024]))
+    kt = mx.bf16_from_bits(np.ascontiguousarray(k[:, :, :nkv]))
+    few = mx.softmax_rows(qt, kt, 900, 124)[..., :nkv]
+    if nkv == 1025:  # 768 row tiles: the undivided launch
+        many = mx.softmax_rows(qt, kt)[..., :nkv]
+        assert torch.equal(many[:, :, 900:], few)
+        del many
+    for mode, gamma in (("uos", 1.0), ("ocp_vanilla", 4.0), ("uos", 1.37)):
+        fused = mx.attention_rowsum_diag(qt, kt, mode, gamma).cpu().numpy()[:, :, 900:]
+        p = torch.zeros((1, 96, 124, (nkv + 3) // 4 * 4), dtype=torch.float32, device="cuda")
+        p[..., :nkv] = few
+        two = mx.rowsum_diag(p, nkv, mode, gamma).cpu().numpy().reshape(fused.shape)
+        _same_stats(fused, two, f"Nkv={nkv} {mode} gamma={gamma}")
+    _softmax_check(mx, np.ascontiguousarray(q[:, :2, :1024]), np.ascontiguousarray(k[:, :2, :nkv]), 1000, 24,
+                   f"Nkv={nkv}")
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("gamma", [1.0, 8.0, 65536.0, 1.37])
+def test_rowsum_diag_edges(mx, mode, gamma):
+    """Lengths around the step of 2048, blocks of entries on thresholds, all
+    zero, all saturating, and down to the smallest scales."""
+    for N in (1, 7, 8, 31, 33, 2047, 2048, 2049, 4100):
+        ld = (N + 3) // 4 * 4 + 4
+        P = np.full((6, ld), 0.3, np.float32)
+        P[0, :N] = _random_rows(N, 1, N, 3.0)[0]
+        P[1, :N] = np.resize(np.float32([0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0, 6.0, 7.25, 0.24999999, 0.25000003]), N)
+        P[1, :N] *= np.float32(2.0 ** -12)
+        P[2, :N] = 0.0
+        P[3, :N] = np.float32(2.0 ** -9 * 7.9)
+        P[4, :N] = np.float32(2.0 ** -100) * P[0, :N]
+        P[5, :N] = np.resize(np.float32([1e-4, 1e-9, 1e-20, 1e-38, 0.0]), N)
+        _diag_check(mx, P, N, mode, gamma, f"{mode} gamma={gamma} N={N}")
+
+
 def test_fused_diag_720p_sampled_rows(mx):
     """Whole 720p tensor diagnosed in one launch; sampled rows equal the
     diagnostic of the same rows materialized."""
