@@ -289,7 +289,8 @@ const char* mxattn_last_error(void);
  * ordered, from a memory pool that belongs to the library (one per device,
  * created on first use; the device's default pool is left as it is).  The
  * pool keeps freed workspace for the next call rather than returning it to
- * the driver.  mxattn_release_workspace returns all of the current device's
+ * the driver; one block of at most 64 MiB per device stays allocated for the
+ * calls on the null stream that fit it.  mxattn_release_workspace returns all of the current device's
  * cached workspace that no call still uses; call it after the streams that
  * ran the library's calls have completed, e.g. before a phase of a pipeline
  * that needs the memory.  Returns MXATTN_OK or MXATTN_ERR_HIP. */

@@ -3,7 +3,7 @@
 // Argument validation happens before any HIP call, so every error path is
 // free of device work.  The only global state is the library's own
 // stream-ordered workspace pool per device (created once, see
-// workspace_alloc).
+// workspace_alloc) and the block it keeps per device (KeptBlock).
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -97,6 +97,88 @@ hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
     return hipMallocAsync(p, bytes, s);
 }
 
+// A stream-ordered allocation and its free cost the host about 15 us, several
+// times the launches of a short call.  So each device keeps one block for the
+// calls on its null stream, which is never destroyed and runs them in the order
+// they were enqueued: the next call may overwrite the block without waiting.
+// `m` is held while a call is enqueued, so that two threads' launches cannot
+// interleave on one block; a call that finds it held, one on another stream
+// (whose handle may be destroyed and given out again while its work still
+// runs, or which may be captured) and one that needs more than kKeptMost take
+// their workspace from the pool as they go.  Host time of a call of 2 heads x
+// 512 tokens through the C ABI: 22.3 us with the pool, 5.8 us with the block.
+constexpr size_t kKeptMost = (size_t)64 << 20;
+struct KeptBlock {
+    std::mutex m;
+    void* p = nullptr;
+    size_t bytes = 0;
+};
+KeptBlock g_kept[kMaxDevices];
+
+// The workspace of one call, given back when the call has been enqueued.
+class Workspace {
+  public:
+    // The status of taking `bytes` for a call on `s`.
+    int take(size_t bytes, hipStream_t s) {
+        stream_ = s;
+        int dev = -1;
+        if (s == nullptr && bytes <= kKeptMost && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
+            KeptBlock& k = g_kept[dev];
+            std::unique_lock<std::mutex> lock(k.m, std::try_to_lock);
+            if (lock.owns_lock()) {
+                if (k.bytes < bytes) grow(k, bytes);
+                if (k.bytes >= bytes) {
+                    lock_ = std::move(lock);
+                    p_ = k.p;
+                    return MXATTN_OK;
+                }
+            }
+        }
+        hipError_t e = workspace_alloc(&p_, bytes, s);
+        if (e != hipSuccess || !p_) {
+            p_ = nullptr;
+            set_error("workspace allocation", e);
+            return MXATTN_ERR_OOM;
+        }
+        return MXATTN_OK;
+    }
+    uint8_t* get() const { return static_cast<uint8_t*>(p_); }
+    // Gives the workspace back; the call's status, or that of the free.
+    int give_back(int st) {
+        if (lock_.owns_lock()) {
+            lock_.unlock();
+            return st;
+        }
+        hipError_t e = hipFreeAsync(p_, stream_);
+        if (st == MXATTN_OK && e != hipSuccess) {
+            set_error("hipFreeAsync", e);
+            st = MXATTN_ERR_HIP;
+        }
+        return st;
+    }
+
+  private:
+    // A block of at least `bytes` (the next power of two from 1 MiB on) in place
+    // of k's; k is empty if it cannot be had.
+    static void grow(KeptBlock& k, size_t bytes) {
+        if (k.p) (void)hipFreeAsync(k.p, nullptr);
+        k.p = nullptr;
+        k.bytes = 0;
+        size_t n = (size_t)1 << 20;
+        while (n < bytes) n *= 2;
+        void* p = nullptr;
+        if (workspace_alloc(&p, n, nullptr) != hipSuccess || !p) {
+            (void)hipGetLastError();
+            return;
+        }
+        k.p = p;
+        k.bytes = n;
+    }
+    void* p_ = nullptr;
+    hipStream_t stream_ = nullptr;
+    std::unique_lock<std::mutex> lock_;
+};
+
 }  // namespace
 
 extern "C" {
@@ -111,6 +193,21 @@ int mxattn_release_workspace(void) {
         return MXATTN_ERR_HIP;
     }
     if (dev < 0 || dev >= kMaxDevices) return MXATTN_OK;
+    {
+        KeptBlock& k = g_kept[dev];
+        std::lock_guard<std::mutex> lock(k.m);
+        if (k.p) {
+            (void)hipFreeAsync(k.p, nullptr);
+            k.p = nullptr;
+            k.bytes = 0;
+            // the free is through before the trim (waiting is allowed also while
+            // another stream is captured)
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (hipStreamSynchronize(nullptr) != hipSuccess) (void)hipGetLastError();
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        }
+    }
     hipMemPool_t pool = g_pools[dev].pool.load();
     if (!pool) return MXATTN_OK;  // no workspace was ever taken on this device
     e = hipMemPoolTrimTo(pool, 0);
@@ -208,24 +305,15 @@ int mxattn_qmax_sse(const void* x, int block_axis, const double* qs, int nq, dou
     if (int st = check_shape(B, H, N, d)) return st;
     if (!aligned(x, 16) || !aligned(sse, 8)) return MXATTN_ERR_ALIGN;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    void* ws = nullptr;
-    hipError_t e = workspace_alloc(&ws, (size_t)mxattn::qmax_sse_workspace_bytes(block_axis, B * H, N), s);
-    if (e != hipSuccess || !ws) {
-        set_error("workspace allocation", e);
-        return MXATTN_ERR_OOM;
-    }
+    Workspace ws;
+    if (int st = ws.take((size_t)mxattn::qmax_sse_workspace_bytes(block_axis, B * H, N), s)) return st;
     int st = MXATTN_OK;
-    e = mxattn::launch_qmax_sse(x, block_axis, qs, nq, sse, ws, B * H, N, s);
+    hipError_t e = mxattn::launch_qmax_sse(x, block_axis, qs, nq, sse, ws.get(), B * H, N, s);
     if (e != hipSuccess) {
         set_error("sse sweep launch", e);
         st = MXATTN_ERR_HIP;
     }
-    e = hipFreeAsync(ws, s);
-    if (st == MXATTN_OK && e != hipSuccess) {
-        set_error("hipFreeAsync", e);
-        st = MXATTN_ERR_HIP;
-    }
-    return st;
+    return ws.give_back(st);
 }
 
 int mxattn_softmax_rows(const void* q, const void* k, float* p, int64_t B, int64_t H, int64_t Nq,
@@ -424,23 +512,11 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
                                    d, mode))
         return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    void* ws = nullptr;
     const size_t scale_bytes = (size_t)mxattn::tile_scales_bytes(B * H, Nkv);
-    hipError_t e =
-        workspace_alloc(&ws, scale_bytes + mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv)), s);
-    if (e != hipSuccess || !ws) {
-        set_error("workspace allocation", e);
-        return MXATTN_ERR_OOM;
-    }
-    int st = launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales,
-                                  static_cast<uint8_t*>(ws), static_cast<uint8_t*>(ws) + scale_bytes, out, B, H, Nq,
-                                  Nkv, mode, s);
-    e = hipFreeAsync(ws, s);
-    if (st == MXATTN_OK && e != hipSuccess) {
-        set_error("hipFreeAsync", e);
-        st = MXATTN_ERR_HIP;
-    }
-    return st;
+    Workspace ws;
+    if (int st = ws.take(scale_bytes + mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv)), s)) return st;
+    return ws.give_back(launch_attend_public(q_codes, q_scales, k_codes, k_scales, v_codes, v_scales, ws.get(),
+                                             ws.get() + scale_bytes, out, B, H, Nq, Nkv, mode, s));
 }
 
 // ---- the entry point that allocates nothing
@@ -553,13 +629,9 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     const size_t split = mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv));
     const size_t total = up(q_codes) + up(k_codes) + up(v_codes) + up(q_scales) + up(tiled) + split;
 
-    void* ws = nullptr;
-    hipError_t e = workspace_alloc(&ws, total, s);
-    if (e != hipSuccess || !ws) {
-        set_error("workspace allocation", e);
-        return MXATTN_ERR_OOM;
-    }
-    uint8_t* p = static_cast<uint8_t*>(ws);
+    Workspace ws;
+    if (int st = ws.take(total, s)) return st;
+    uint8_t* p = ws.get();
     uint8_t* qc = p;
     p += up(q_codes);
     uint8_t* kc = p;
@@ -585,18 +657,13 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     a.ntiles = (int)ntiles;
     a.qtiles = (int)((Nq + 127) / 128);
     int st = MXATTN_OK;
-    if ((e = mxattn::launch_prepare_operands(a, rule_of(mode), !q_fused, s)) != hipSuccess) {
+    if (hipError_t e = mxattn::launch_prepare_operands(a, rule_of(mode), !q_fused, s)) {
         set_error("quantize launch", e);
         st = MXATTN_ERR_HIP;
     } else {
         st = launch_attend(q_fused ? q : nullptr, qc, qs, kc, vc, true, sc, sc + up(tiled), out, B, H, Nq, Nkv, mode, s);
     }
-    e = hipFreeAsync(ws, s);
-    if (st == MXATTN_OK && e != hipSuccess) {
-        set_error("hipFreeAsync", e);
-        st = MXATTN_ERR_HIP;
-    }
-    return st;
+    return ws.give_back(st);
 }
 
 int mxattn_forward(const void* q, const void* k, const void* v, void* out, int64_t B, int64_t H,

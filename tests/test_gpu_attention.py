@@ -208,6 +208,46 @@ def test_forward_operands_equal_the_public_ones(mx, Nq, Nkv):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (Nq, Nkv, mode)
 
 
+def test_workspace_across_streams_and_threads(mx):
+    """Calls on the null stream share one kept block of workspace, those on
+    other streams and of a second thread at the same time do not: every output
+    equals the one computed alone, with sizes that grow the block, after it was
+    given back, and beyond its limit."""
+    import threading
+
+    shapes = [(1, 2, 300), (2, 3, 1000), (1, 1, 40), (1, 8, 4000), (1, 40, 16000)]  # the last takes 87 MB
+    data = []
+    for i, (B, H, N) in enumerate(shapes):
+        g = torch.Generator(device="cuda").manual_seed(i)
+        t = [torch.randn((B, H, N, 128), generator=g, device="cuda").bfloat16() for _ in range(3)]
+        data.append(t + [mx.forward(*t, "uos_pnq")])
+    torch.cuda.synchronize()
+    mx.release_workspace()
+    bad = []
+
+    def work(stream, order):
+        for i in order:
+            q, k, v, want = data[i]
+            with torch.cuda.stream(stream):
+                out = mx.forward(q, k, v, "uos_pnq")
+                same = torch.equal(out.view(torch.int16), want.view(torch.int16))
+            if not same:
+                bad.append((stream, i))
+
+    null, side = torch.cuda.default_stream(), torch.cuda.Stream()
+    orders = ([0, 3, 1, 2, 4, 0, 1], [2, 1, 0, 3, 1, 4, 2], [1, 0, 2, 3, 0, 2, 1])
+    threads = [threading.Thread(target=work, args=a) for a in zip((null, null, side), orders)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    mx.release_workspace()
+    work(null, [0, 2])
+    torch.cuda.synchronize()
+    assert not bad, bad
+
+
 def _edge_q_rows(q):
     """Overwrite the first query rows of every head with values that exercise
     the quantizer's scale rule: an all-zero block (sigma = 1), bf16
