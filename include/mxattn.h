@@ -139,8 +139,9 @@ int mxattn_quantize_qmax(const void* x, uint8_t* codes, uint8_t* scales, int blo
  * Sums are formed in fp64 (each element's squared error exactly); the order
  * of additions within a workgroup is not fixed, so repeated calls may differ
  * in the last bits.  Uses stream-ordered workspace (the library's pool,
- * see mxattn_release_workspace): 2056 bytes per workgroup, about 2048 workgroups or one per
- * (batch, head) if there are more, so about 2 KiB * max(B*H, 2048).
+ * see mxattn_release_workspace): 2056 bytes per workgroup, at most 2048
+ * workgroups or one per (batch, head) if there are more, so at most about
+ * 2 KiB * max(B*H, 2048).
  * Returns MXATTN_OK, MXATTN_ERR_OOM, or another error status. */
 int mxattn_qmax_sse(const void* x, int block_axis, const double* qs, int nq, double* sse, int64_t B,
                     int64_t H, int64_t N, int64_t d, void* stream);

@@ -34,7 +34,9 @@ namespace mxattn {
 namespace {
 
 constexpr int kBins = 257;          // A[0..127], B[0..127], C
-constexpr int kTargetGroups = 2048;  // workgroups per launch (8 per CU)
+// Workgroups that are resident at once (8 and 3 per CU of 256): a launch has at
+// most as many where it can, so that no second round runs nearly empty.
+constexpr int kHeaddimSlots = 2048, kTokensSlots = 768;
 constexpr int kTokGroup = 128;       // tokens staged per workgroup step (token blocks)
 
 struct BoundaryList {
@@ -55,9 +57,9 @@ __device__ __forceinline__ float pair_sse(uint32_t pair, int e) {
     const auto r = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 0);
     // 2^-e as a normal fp32 (e <= 126 here: bf16 maxima have E <= 254)
     const float inv = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
-    const float d0 = bf16_lo(pair) * inv - r[0];
-    const float d1 = bf16_hi(pair) * inv - r[1];
-    return fmaf(d0, d0, d1 * d1);
+    const float d0 = __builtin_fmaf(bf16_lo(pair), inv, -r[0]);
+    const float d1 = __builtin_fmaf(bf16_hi(pair), inv, -r[1]);
+    return __builtin_fmaf(d0, d0, d1 * d1);
 }
 
 // Squared error of 8 elements (4 bf16 pairs) under exponent e.  Each term is
@@ -67,6 +69,13 @@ __device__ __forceinline__ float pair_sse(uint32_t pair, int e) {
 // the error of a 7-addition fp32 sum of nonnegative terms, 7 * 2^-24 of it.
 __device__ __forceinline__ double oct_sse(uint32_t a, uint32_t b, uint32_t c, uint32_t d, int e) {
     return (double)((pair_sse(a, e) + pair_sse(b, e)) + (pair_sse(c, e) + pair_sse(d, e)));
+}
+
+// Magnitude bits of the larger of each half of two bf16 pairs (signs cleared in b).
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max_pair(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                                                  __builtin_bit_cast(u16x2, b & 0x7FFF7FFFu)));
 }
 
 __device__ __forceinline__ void hist_zero(double* h) {
@@ -80,10 +89,23 @@ __device__ __forceinline__ void hist_add(double* h, uint32_t mbits, double sp, d
     if (F == 0) atomicAdd(&h[256], sm);
 }
 
-// Blocks along d (rows of 128 = 4 blocks): as the head-dim quantizer, each
-// thread owns 8 consecutive elements and 4 adjacent lanes form a block.  A
-// workgroup covers rows [c * rows_per_chunk, ...) of one head, 16 rows per
-// step.
+// The value of lane i ^ 1 (a DPP move: no LDS traffic).
+__device__ __forceinline__ uint32_t swap1(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);
+}
+__device__ __forceinline__ double swap1(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)swap1((uint32_t)(b >> 32)) << 32 | swap1((uint32_t)b));
+}
+
+// Blocks along d (rows of 128 = 4 blocks).  A lane owns 16 consecutive
+// elements, so two lanes form a block: they add their sums to each other's, and
+// one adds the block to A, the other to B.  (Four lanes per block, one of which
+// added all sums, took 98 us instead of 80 for 40 heads x 32760 rows, of which
+// the loads take 61: fp64 exchanges and atomics come on top of about 10 vector
+// instructions per element.)  A workgroup
+// covers rows [c * rows_per_chunk, ...) of one head, 32 rows per step, the next
+// step's loads issued before a step is worked on.
 __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __restrict__ x,
                                                                double* __restrict__ partial,
                                                                int64_t N, int64_t rows_per_chunk,
@@ -95,38 +117,47 @@ __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __re
 
     const int64_t r0 = (int64_t)c * rows_per_chunk;
     const int64_t r1 = min(N, r0 + rows_per_chunk);
-    const uint4* src = x + (int64_t)bh * N * 16;
-    for (int64_t base = r0; base < r1; base += 16) {  // same trip count in every lane
-        const int64_t row = base + (threadIdx.x >> 4);
-        const bool valid = row < r1;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (valid) v = src[row * 16 + (threadIdx.x & 15)];
-        uint32_t m = 0;
-        m = max(m, v.x & 0x7FFFu);
-        m = max(m, (v.x >> 16) & 0x7FFFu);
-        m = max(m, v.y & 0x7FFFu);
-        m = max(m, (v.y >> 16) & 0x7FFFu);
-        m = max(m, v.z & 0x7FFFu);
-        m = max(m, (v.z >> 16) & 0x7FFFu);
-        m = max(m, v.w & 0x7FFFu);
-        m = max(m, (v.w >> 16) & 0x7FFFu);
-        m = max(m, (uint32_t)__shfl_xor((int)m, 1));
-        m = max(m, (uint32_t)__shfl_xor((int)m, 2));
+    const uint4* src = x + ((int64_t)bh * N) * 16 + 2 * (threadIdx.x & 7);
+    auto fetch = [&](int64_t base, uint4 (&v)[2]) {
+        const int64_t row = base + (threadIdx.x >> 3);
+        v[0] = v[1] = make_uint4(0, 0, 0, 0);
+        if (row < r1) {
+            v[0] = src[row * 16];
+            v[1] = src[row * 16 + 1];
+        }
+    };
+    uint4 next[2];
+    fetch(r0, next);
+    for (int64_t base = r0; base < r1; base += 32) {  // same trip count in every lane
+        const uint4 v0 = next[0], v1 = next[1];
+        fetch(base + 32, next);
+        const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        uint32_t m2 = 0;
+#pragma unroll
+        for (int e = 0; e < 8; e++) m2 = max_pair(m2, w[e]);
+        m2 = max_pair(m2, swap1(m2));
+        const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
         const int E = (int)(m >> 7);
         const int ep = clamp_e(E - 128), e0 = clamp_e(E - 129), em = clamp_e(E - 130);
+        auto lane_sse = [&](int e) {
+            return oct_sse(v0.x, v0.y, v0.z, v0.w, e) + oct_sse(v1.x, v1.y, v1.z, v1.w, e);
+        };
+        double sp = lane_sse(ep);
+        double s0 = lane_sse(e0);
+        sp += swap1(sp);
+        s0 += swap1(s0);
         // E - 130 is used only for a power-of-two maximum (F = 0)
-        const bool pow2 = (m & 0x7Fu) == 0;
-        double sp = oct_sse(v.x, v.y, v.z, v.w, ep);
-        double s0 = oct_sse(v.x, v.y, v.z, v.w, e0);
-        double sm = pow2 ? oct_sse(v.x, v.y, v.z, v.w, em) : 0.0;
-        sp += __shfl_xor(sp, 1);
-        s0 += __shfl_xor(s0, 1);
-        sm += __shfl_xor(sm, 1);
-        sp += __shfl_xor(sp, 2);
-        s0 += __shfl_xor(s0, 2);
-        sm += __shfl_xor(sm, 2);
-        if (valid && (threadIdx.x & 3) == 0)
-            hist_add(hist, m, ldexp(sp, 2 * ep), ldexp(s0, 2 * e0), ldexp(sm, 2 * em));
+        const int F = (int)(m & 0x7Fu);
+        if (F == 0) {
+            double sm = lane_sse(em);
+            sm += swap1(sm);
+            if (threadIdx.x & 1) atomicAdd(&hist[256], ldexp(sm, 2 * em));
+        }
+        // rows past the end hold zeros, which add nothing
+        if (threadIdx.x & 1)
+            atomicAdd(&hist[128 + F], ldexp(s0, 2 * e0));
+        else
+            atomicAdd(&hist[F], ldexp(sp, 2 * ep));
     }
     __syncthreads();
     double* dst = partial + (int64_t)blockIdx.x * kBins;
@@ -150,6 +181,18 @@ __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __res
     const uint4* src = x + (int64_t)bh * N * 16;
     const int g0 = c * groups_per_chunk, g1 = min(groups, g0 + groups_per_chunk);
     const int w = tid >> 6, cp = tid & 63;
+    // the next group's loads are in flight while a group is worked on
+    uint4 buf[8];
+    auto fetch = [&](int g) {
+        const int tok0 = g * kTokGroup;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int ch = tid + 256 * k;
+            const int tok = ch >> 4, part = ch & 15;
+            buf[k] = g < g1 && tok0 + tok < N ? src[(int64_t)(tok0 + tok) * 16 + part] : make_uint4(0, 0, 0, 0);
+        }
+    };
+    fetch(g0);
     for (int g = g0; g < g1; g++) {
         const int tok0 = g * kTokGroup;
         __syncthreads();  // previous group's reads (and the zeroed histogram)
@@ -157,22 +200,20 @@ __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __res
         for (int k = 0; k < 8; k++) {
             const int ch = tid + 256 * k;
             const int tok = ch >> 4, part = ch & 15;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (tok0 + tok < N) v = src[(int64_t)(tok0 + tok) * 16 + part];
-            *reinterpret_cast<uint4*>(&tile[tok * 64 + part * 4]) = v;
+            *reinterpret_cast<uint4*>(&tile[tok * 64 + part * 4]) = buf[k];
         }
         __syncthreads();
+        fetch(g + 1);
         if (tok0 + 32 * w >= N) continue;  // block entirely past the sequence end
 
         uint32_t col[32];
-        uint32_t m0 = 0, m1 = 0;
+        uint32_t m2 = 0;
 #pragma unroll
         for (int t = 0; t < 32; t++) {
-            const uint32_t d = tile[(32 * w + t) * 64 + cp];
-            col[t] = d;
-            m0 = max(m0, d & 0x7FFFu);
-            m1 = max(m1, (d >> 16) & 0x7FFFu);
+            col[t] = tile[(32 * w + t) * 64 + cp];
+            m2 = max_pair(m2, col[t]);
         }
+        const uint32_t m0 = m2 & 0xFFFFu, m1 = m2 >> 16;
 #pragma unroll
         for (int ch = 0; ch < 2; ch++) {
             const uint32_t m = ch ? m1 : m0;
@@ -199,32 +240,41 @@ __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __res
     for (int i = tid; i < kBins; i += blockDim.x) dst[i] = hist[i];
 }
 
-// One workgroup per head: sums the chunks' histograms in chunk order, then
-// forms each boundary's total in bin order.
-__global__ __launch_bounds__(256) void sse_reduce_kernel(const double* __restrict__ partial, int chunks,
+// One workgroup per head: sums the chunks' histograms in chunk order (eight
+// loads in flight: 22 -> 5 us at 40 heads), then four lanes per boundary form its total, each over a
+// quarter of the bins in order.
+__global__ __launch_bounds__(320) void sse_reduce_kernel(const double* __restrict__ partial, int chunks,
                                                          BoundaryList bl, int nq, double* __restrict__ sse) {
     __shared__ double hist[kBins];
     const int bh = blockIdx.x;
     const double* src = partial + (int64_t)bh * chunks * kBins;
-    for (int i = threadIdx.x; i < kBins; i += blockDim.x) {
+    if (threadIdx.x < kBins) {
+        const double* p = src + threadIdx.x;
         double acc = 0.0;
-        for (int c = 0; c < chunks; c++) acc += src[(int64_t)c * kBins + i];
-        hist[i] = acc;
+        int c = 0;
+        for (; c + 8 <= chunks; c += 8) {
+            double v[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] = p[(int64_t)(c + e) * kBins];
+#pragma unroll
+            for (int e = 0; e < 8; e++) acc += v[e];
+        }
+        for (; c < chunks; c++) acc += p[(int64_t)c * kBins];
+        hist[threadIdx.x] = acc;
     }
     __syncthreads();
-    const int j = threadIdx.x;
-    if (j < nq) {
-        double tot = 0.0;
-        for (int F = 0; F < 128; F++) {
-            if (F > bl.thr[j])
-                tot += hist[F];
-            else if (F == 0 && bl.down[j])
-                tot += hist[256];
-            else
-                tot += hist[128 + F];
-        }
-        sse[(int64_t)bh * nq + j] = tot;
+    const int j = threadIdx.x >> 2, quarter = threadIdx.x & 3;
+    if (j >= kMaxBoundaries) return;
+    const int thr = bl.thr[j], down = bl.down[j];
+    double tot = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < 32; i++) {
+        const int F = 32 * quarter + i;
+        tot += hist[F > thr ? F : (F == 0 && down ? 256 : 128 + F)];
     }
+    tot += __shfl_xor(tot, 1);
+    tot += __shfl_xor(tot, 2);
+    if (quarter == 0 && j < nq) sse[(int64_t)bh * nq + j] = tot;
 }
 
 // Workgroups per head and the work each takes.
@@ -234,15 +284,15 @@ struct Split {
 };
 
 Split split_of(int axis, int64_t BH, int64_t N) {
-    const int64_t units = axis == 3 ? (N + 15) / 16 : (N + kTokGroup - 1) / kTokGroup;
-    int64_t chunks = (kTargetGroups + BH - 1) / BH;
+    const int64_t units = axis == 3 ? (N + 31) / 32 : (N + kTokGroup - 1) / kTokGroup;
+    int64_t chunks = (axis == 3 ? kHeaddimSlots : kTokensSlots) / BH;
     if (chunks > units) chunks = units;
     if (chunks < 1) chunks = 1;
-    int64_t per = (units + chunks - 1) / chunks;  // in 16-row steps or token groups
+    int64_t per = (units + chunks - 1) / chunks;  // in 32-row steps or token groups
     chunks = (units + per - 1) / per;
     Split s;
     s.chunks = (int)chunks;
-    s.per_chunk = axis == 3 ? per * 16 : per;
+    s.per_chunk = axis == 3 ? per * 32 : per;
     return s;
 }
 
@@ -273,7 +323,7 @@ hipError_t launch_qmax_sse(const void* x, int axis, const double* qs, int nq, do
         bl.thr[j] = b.thr;
         bl.down[j] = b.pow2_down;
     }
-    sse_reduce_kernel<<<dim3((unsigned)BH), 256, 0, stream>>>(partial, sp.chunks, bl, nq, sse);
+    sse_reduce_kernel<<<dim3((unsigned)BH), 320, 0, stream>>>(partial, sp.chunks, bl, nq, sse);
     return hipGetLastError();
 }
 
