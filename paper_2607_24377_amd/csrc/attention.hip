@@ -344,13 +344,10 @@ __device__ __forceinline__ QRaw q_raw(const AttnArgs& a, int64_t row, int h) {
 // the gfx950 FP4 conversion, so the codes are bit-identical to that kernel's.
 template <int kRule>
 __device__ __forceinline__ v8i quantize_q_block(const uint4* v, int& sbyte) {
-    uint32_t m = 0;
+    uint32_t m2 = 0;
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-#pragma unroll
-        for (int e = 0; e < 4; e++) m = max(m, max(w[e] & 0x7FFFu, (w[e] >> 16) & 0x7FFFu));
-    }
+    for (int k = 0; k < 4; k++) m2 = max_halves(m2, v[k]);
+    const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
     const uint32_t sb = (m == 0) ? 127u : (uint32_t)(scale_exponent_bf16<kRule>(m) + 127);
     const float sf = e8m0_as_f32(sb);
     uint32_t c[4];
@@ -393,6 +390,16 @@ __device__ __forceinline__ void mask_tail(v16f (&S)[2][2], int valid) {
         }
 }
 
+// What the scores of the last tile of N keys accumulate onto: -inf past the
+// end, else 0; [h][c][j][i] for key 64 c + 32 h + 16 j + i of the tile.
+constexpr int kTailFloats = 128;
+__device__ __forceinline__ void tail_table(float* tail, int N, int tid) {
+    if (tid < kTailFloats) {
+        const int h = tid >> 6, c = (tid >> 5) & 1, ji = tid & 31;
+        tail[tid] = 64 * c + 32 * h + ji < N - (N - 1) / 128 * 128 ? 0.f : -__builtin_inff();
+    }
+}
+
 // One KV tile of Algorithm 2 for the wave's 32 query rows, read from the LDS
 // stage at `st`: S^T = K^ Q^T, the online-softmax update of (m, l), P^ and
 // O~^T += V^T P^T.  Reads LDS only; the caller owns loads and barriers.
@@ -400,8 +407,8 @@ __device__ __forceinline__ void mask_tail(v16f (&S)[2][2], int valid) {
 // them (the rescale by alpha = 0 of a zero O~ and l is skipped, and the first
 // products accumulate onto zero), so they need no initial values.
 template <int kRule, bool kPnq, bool kFirst = false>
-__device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo, int tile, int N, int h,
-                                            const QOperands& qo, const v8i& sel, float& m, RowSum& rs,
+__device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo, const float* tail, int tile, int N,
+                                            int h, const QOperands& qo, const v8i& sel, float& m, RowSum& rs,
                                             v16f (&O)[4]) {
     const float cl = 0.12751743082459868f;  // fp32(log2(e) / sqrt(128))
     const v8i& qB0 = qo.b0;
@@ -421,25 +428,35 @@ __device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo
         kop[c][1][1] = fp4_v(ld128<kKcOff + 1 * 2048>(st + 4096 * c, lo.hi));
     }
 
-    // ---- S^T = K^ Q^T: S[c][j][i] is key 64c + 32h + 16j + i of the tile
+    // ---- S^T = K^ Q^T: S[c][j][i] is key 64c + 32h + 16j + i of the tile.  In
+    // the ragged last tile the products accumulate onto -inf for keys past the
+    // end (and onto 0 for the others, as elsewhere), read from the table of
+    // tail_table: masking takes no vector instruction.  A second chunk with no
+    // key at all is left out.
     v16f S[2][2];
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
+    auto products = [&](int c, int j, v16f acc) {
         const int sreg = c == 0 ? (int)ksb.x : (int)ksb.y;
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            v16f acc;
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[i] = 0.f;
-            if (j == 0) {
-                acc = mfma_fp4<0>(kop[c][j][0], qB0, acc, sreg, qS0);
-                acc = mfma_fp4<1>(kop[c][j][1], qB1, acc, sreg, qS1);
-            } else {
-                acc = mfma_fp4<2>(kop[c][j][0], qB0, acc, sreg, qS0);
-                acc = mfma_fp4<3>(kop[c][j][1], qB1, acc, sreg, qS1);
-            }
-            S[c][j] = acc;
+        if (j == 0) {
+            acc = mfma_fp4<0>(kop[c][j][0], qB0, acc, sreg, qS0);
+            return mfma_fp4<1>(kop[c][j][1], qB1, acc, sreg, qS1);
         }
+        acc = mfma_fp4<2>(kop[c][j][0], qB0, acc, sreg, qS0);
+        return mfma_fp4<3>(kop[c][j][1], qB1, acc, sreg, qS1);
+    };
+    const int left = N - tile * 128;  // keys from the tile's first on
+    const bool two = left > 64;       // the second chunk has keys
+    if (left >= 128) {
+        const v16f zero = {};
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int j = 0; j < 2; j++) S[c][j] = products(c, j, zero);
+    } else {
+        const v16f* tab = reinterpret_cast<const v16f*>(tail) + 4 * h;
+#pragma unroll
+        for (int j = 0; j < 2; j++) S[0][j] = products(0, j, tab[j]);
+#pragma unroll
+        for (int j = 0; j < 2; j++) S[1][j] = two ? products(1, j, tab[2 + j]) : tab[2 + j];
     }
 
     // ---- V^ operands for the PV products (read now, used after softmax):
@@ -449,18 +466,6 @@ __device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo
     for (int n = 0; n < 4; n++) {
         vop[n][0] = fp4_v(ld128<kVcOff>(st + 2048 * n, lo.lo));
         vop[n][1] = fp4_v(ld128<kVcOff>(st + 2048 * n, lo.hi));
-    }
-
-    // ---- mask keys past the end of the sequence (last tile only)
-    const int k0 = tile * 128;
-    if (k0 + 128 > N) {
-#pragma unroll
-        for (int c = 0; c < 2; c++)
-#pragma unroll
-            for (int j = 0; j < 2; j++)
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    if (k0 + 64 * c + 32 * h + 16 * j + i >= N) S[c][j][i] = -__builtin_inff();
     }
 
     // ---- running maximum: the block maxima (one P~ block per lane and
@@ -493,6 +498,7 @@ __device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo
     float lsum = 0.f;
 #pragma unroll
     for (int c = 0; c < 2; c++) {
+        if (c == 1 && !two) break;
         const float mb = __builtin_amdgcn_exp2f(__builtin_fmaf(bmax[c], cl, -m_new));
         const uint32_t sbits = p_scale_bits<kRule>(__builtin_bit_cast(uint32_t, mb));
         const float sf = __builtin_bit_cast(float, sbits);
@@ -1093,6 +1099,7 @@ static_assert(kStagedStoreMaxTiles < kResidentTiles && kWaves * kOutStageBytes <
 template <int kRule, bool kPnq, bool kQraw>
 __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kResidentTiles * kStageBytes];
+    __shared__ __attribute__((aligned(64))) float tail[kTailFloats];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
@@ -1119,6 +1126,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArg
 
     const v8i sel = row_sum_selector(lane);
     const LaneOff lo = lane_off(q, h, lane);
+    tail_table(tail, N, tid);
 
     __builtin_amdgcn_s_waitcnt(0);  // this wave's direct LDS loads landed
     __syncthreads();                // and every other wave's
@@ -1159,9 +1167,9 @@ __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArg
         float m;
         RowSum rs;
         v16f O[4];
-        attend_tile<kRule, kPnq, true>(lds, lo, 0, N, h, qo, sel, m, rs, O);
+        attend_tile<kRule, kPnq, true>(lds, lo, tail, 0, N, h, qo, sel, m, rs, O);
         for (int tile = 1; tile < ntiles; tile++)
-            attend_tile<kRule, kPnq>(lds + tile * kStageBytes, lo, tile, N, h, qo, sel, m, rs, O);
+            attend_tile<kRule, kPnq>(lds + tile * kStageBytes, lo, tail, tile, N, h, qo, sel, m, rs, O);
 
         const QOperands qn = operands(next);
         store_rows<kPnq>(a, rowbase, qi, q, h, lane, ostage, staged, rs, O);

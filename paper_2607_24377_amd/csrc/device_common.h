@@ -74,6 +74,18 @@ __device__ __forceinline__ int block_exponent_bf16(uint32_t mbits, Boundary b) {
         return scale_exponent_bf16<kRule>(mbits);
 }
 
+// Block maxima of bf16 magnitudes: the larger of each 16-bit half of m and the
+// four pairs of v, signs cleared (packed 16-bit maxima: two instructions per
+// pair; halves taken apart first they are four and a half).
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max_halves(uint32_t m, uint32_t v) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m),
+                                                                  __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu)));
+}
+__device__ __forceinline__ uint32_t max_halves(uint32_t m, const uint4& v) {
+    return max_halves(max_halves(max_halves(max_halves(m, v.x), v.y), v.z), v.w);
+}
+
 // The fp32 whose exponent field is the E8M0 byte: the scale operand of the
 // gfx950 FP4 conversions, which divide by 2^(exponent field - 127).
 __device__ __forceinline__ float e8m0_as_f32(uint32_t byte) {

@@ -71,13 +71,6 @@ __device__ __forceinline__ double oct_sse(uint32_t a, uint32_t b, uint32_t c, ui
     return (double)((pair_sse(a, e) + pair_sse(b, e)) + (pair_sse(c, e) + pair_sse(d, e)));
 }
 
-// Magnitude bits of the larger of each half of two bf16 pairs (signs cleared in b).
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t max_pair(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
-                                                                  __builtin_bit_cast(u16x2, b & 0x7FFF7FFFu)));
-}
-
 __device__ __forceinline__ void hist_zero(double* h) {
     for (int i = threadIdx.x; i < kBins; i += blockDim.x) h[i] = 0.0;
 }
@@ -131,11 +124,8 @@ __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __re
     for (int64_t base = r0; base < r1; base += 32) {  // same trip count in every lane
         const uint4 v0 = next[0], v1 = next[1];
         fetch(base + 32, next);
-        const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-        uint32_t m2 = 0;
-#pragma unroll
-        for (int e = 0; e < 8; e++) m2 = max_pair(m2, w[e]);
-        m2 = max_pair(m2, swap1(m2));
+        uint32_t m2 = max_halves(max_halves(0u, v0), v1);
+        m2 = max_halves(m2, swap1(m2));
         const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
         const int E = (int)(m >> 7);
         const int ep = clamp_e(E - 128), e0 = clamp_e(E - 129), em = clamp_e(E - 130);
@@ -211,7 +201,7 @@ __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __res
 #pragma unroll
         for (int t = 0; t < 32; t++) {
             col[t] = tile[(32 * w + t) * 64 + cp];
-            m2 = max_pair(m2, col[t]);
+            m2 = max_halves(m2, col[t]);
         }
         const uint32_t m0 = m2 & 0xFFFFu, m1 = m2 >> 16;
 #pragma unroll

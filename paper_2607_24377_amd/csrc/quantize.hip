@@ -69,17 +69,10 @@ template <int kRule>
 __device__ __forceinline__ uint32_t quantize_chunk(uint4 v, Boundary bq, uint32_t& sbyte) {
     // block maximum of |x| on the bf16 bit patterns (order-preserving for
     // nonnegative finite values)
-    uint32_t m = 0;
-    m = max(m, v.x & 0x7FFFu);
-    m = max(m, (v.x >> 16) & 0x7FFFu);
-    m = max(m, v.y & 0x7FFFu);
-    m = max(m, (v.y >> 16) & 0x7FFFu);
-    m = max(m, v.z & 0x7FFFu);
-    m = max(m, (v.z >> 16) & 0x7FFFu);
-    m = max(m, v.w & 0x7FFFu);
-    m = max(m, (v.w >> 16) & 0x7FFFu);
-    m = max(m, (uint32_t)lane_xor<1>((int)m));
-    m = max(m, (uint32_t)lane_xor<2>((int)m));
+    uint32_t m2 = max_halves(0u, v);
+    m2 = max_halves(m2, (uint32_t)lane_xor<1>((int)m2));
+    m2 = max_halves(m2, (uint32_t)lane_xor<2>((int)m2));
+    const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
     // all-zero block: sigma = 1 (Algorithm 1); codes come out as signed zeros
     sbyte = (m == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m, bq) + 127);
     const float sf = e8m0_as_f32(sbyte);
@@ -244,12 +237,10 @@ __device__ __forceinline__ uint32_t cvt_fp4x2_bf16(uint32_t old, uint32_t pair, 
 template <int kRule>
 __device__ __forceinline__ void quantize_token_pair(const uint32_t (&col)[32], Boundary bq, uint4& c0, uint4& c1,
                                                     uint32_t& s0, uint32_t& s1) {
-    uint32_t m0 = 0, m1 = 0;
+    uint32_t m2 = 0;
 #pragma unroll
-    for (int t = 0; t < 32; t++) {
-        m0 = max(m0, col[t] & 0x7FFFu);
-        m1 = max(m1, (col[t] >> 16) & 0x7FFFu);
-    }
+    for (int t = 0; t < 32; t++) m2 = max_halves(m2, col[t]);
+    const uint32_t m0 = m2 & 0xFFFFu, m1 = m2 >> 16;
     s0 = (m0 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m0, bq) + 127);
     s1 = (m1 == 0) ? 127u : (uint32_t)(block_exponent_bf16<kRule>(m1, bq) + 127);
     const float f0 = e8m0_as_f32(s0), f1 = e8m0_as_f32(s1);

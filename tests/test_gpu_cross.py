@@ -71,6 +71,15 @@ def test_cross_ragged_lengths(mx, Nq, Nkv):
         _check(mx, w, mode, range(4), None, w.name)
 
 
+@pytest.mark.parametrize("Nkv", [63, 64, 65, 191, 192, 193, 448, 449])
+def test_cross_tail_chunks(mx, Nkv):
+    # the resident kernel's last tile: keys past the end, and a second chunk
+    # of 64 keys that is left out when it has none
+    w = inputs.Workload(64, f"cross_130x{Nkv}", 1, 2, 130, 128, "cross", Nkv=Nkv)
+    for mode in MODES:
+        _check(mx, w, mode, [0, 1], None, w.name)
+
+
 def test_cross720p_sampled(mx):
     w = inputs.workload("cross720p")
     for mode in ("ocp_vanilla", "uos_pnq"):
