@@ -201,7 +201,7 @@ int mxattn_attention_rowsum_diag(const void* q, const void* k, int64_t B, int64_
  * Quantizes K along d and V along N into stream-ordered workspace (from
  * the library's pool on `stream`, see mxattn_release_workspace; about 0.53
  * bytes per element of each of K and V; calls with few queries over many keys
- * take up to 33 MiB more, for partial results of runs of the keys), then runs
+ * take up to 34 MiB more, for partial results of runs of the keys), then runs
  * the fused kernel, which quantizes Q along d in
  * its prologue with codes bit-identical to mxattn_quantize's; in
  * MXATTN_UOS_PNQ_ROT, Q is rotated and quantized into the workspace first
@@ -249,7 +249,7 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
  * no hipMalloc, hipMallocAsync, hipFree or any allocating routine.  Its one
  * buffer beyond the inputs and `out`, the K^ and V^ scales rearranged into
  * the kernel's operand order (1 KiB per (batch, head) and 128-key tile), is
- * a static device array of MXATTN_NOALLOC_SCRATCH_BYTES, followed by 33 MiB for
+ * a static device array of MXATTN_NOALLOC_SCRATCH_BYTES, followed by 34 MiB for
  * the partial results of calls with few queries over many keys, that each
  * device the library runs on holds until the process ends.  Limit: B * H * ceil(Nkv /
  * 128) <= 32768 (e.g. H = 40 heads of up to 104 832 keys), else

@@ -445,6 +445,10 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
     a.nsplit = mxattn::key_splits(B * H, Nq, Nkv);
     const int64_t total = B * H * a.nchunks * a.nsplit;
     if (a.nsplit > 1) {
+        // a part has at least four tiles
+        const int64_t tiles_per_run = ntiles / a.nsplit;
+        a.score_parts = (int)(tiles_per_run / 4 < mxattn::kScoreParts ? tiles_per_run / 4 : mxattn::kScoreParts);
+        if (a.score_parts < 1) a.score_parts = 1;
         a.part_o = reinterpret_cast<float4*>(split_ws);
         a.part_ml = reinterpret_cast<float2*>(split_ws + total * (128 * 128 * 4));
         a.run_max = reinterpret_cast<float*>(split_ws + total * (128 * (128 * 4 + 8)));

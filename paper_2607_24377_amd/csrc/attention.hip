@@ -920,15 +920,17 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
     PipeState ps;
     ps.m = ps.smax = -__builtin_inff();
     if constexpr (kSplit) {
-        const int s = run - bh * a.nsplit;
+        const int s = (run - bh * a.nsplit) * a.score_parts;  // parts before this run
         if (s > 0) {
-            const float* prior = a.run_max + ((int64_t)bh * a.qtiles + qt) * a.nsplit * kQueryTile + wave * kQw + q;
+            const float* prior =
+                a.run_max + ((int64_t)bh * a.qtiles + qt) * a.nsplit * a.score_parts * kQueryTile + wave * kQw + q;
             float x = prior[0];
-            for (int i = 1; i < s; i += 4) {
-                // past the last one before s the last is read again
-                const float y0 = prior[i * kQueryTile], y1 = prior[min(i + 1, s - 1) * kQueryTile];
-                const float y2 = prior[min(i + 2, s - 1) * kQueryTile], y3 = prior[min(i + 3, s - 1) * kQueryTile];
-                x = max2f(max3f(x, y0, y1), max2f(y2, y3));
+            for (int i = 1; i < s; i += 8) {
+                float y[8];  // past the last one before s the last is read again
+#pragma unroll
+                for (int e = 0; e < 8; e++) y[e] = prior[min(i + e, s - 1) * kQueryTile];
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) x = max3f(x, y[e], y[e + 1]);
             }
             ps.smax = x;
             ps.m = mul_rd(0.12751743082459868f, x);
@@ -991,8 +993,10 @@ __global__ __launch_bounds__(kThreads, 2) void attention_pipelined_kernel(AttnAr
 // depends on the running maximum of all earlier keys, so the runs cannot
 // simply start at m = -inf: this pass finds the largest score of every run
 // but the last (scores only: 8 of a tile's 18 products and none of the
-// exponentials, about a fifth of its time), each run of the main pass then
-// starts from the maximum of the runs before it, so every m, P~ and P^ is
+// exponentials, about a fifth of its time; long runs in up to four parts, so
+// that enough workgroups hide the loads: 73 -> 57 us at 256 x 118800 keys,
+// 24 heads), each run of the main pass then starts from the maximum of the
+// runs before it, so every m, P~ and P^ is
 // that of the undivided loop bit for bit, and split_combine_kernel adds the
 // runs' O~ and l, scaled to the last run's maximum: only the association of
 // these fp32 sums differs.
@@ -1004,15 +1008,19 @@ __global__ __launch_bounds__(kThreads, 2) void split_scores_kernel(AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     const int q = lane & 31, h = lane >> 5;
-    const int runs = a.nsplit - 1;
+    const int parts = (a.nsplit - 1) * a.score_parts;
+    const int wgs = a.total_tiles / a.nsplit * parts;
     const int L = blockIdx.x;
-    const int per_xcd = (a.total_tiles / a.nsplit * runs + 7) / 8;
-    const int logical = (L & 7) * per_xcd + (L >> 3);
-    if (logical >= a.total_tiles / a.nsplit * runs) return;
+    const int logical = (L & 7) * ((wgs + 7) / 8) + (L >> 3);
+    if (logical >= wgs) return;
     const int run = logical / a.qtiles;
     const int qt = logical - run * a.qtiles;
-    const int bh = run / runs, s = run - bh * runs;
-    const SplitRange sr = split_range(a, s);
+    const int bh = run / parts, s = run - bh * parts;  // part s of the head's scored runs
+    SplitRange sr = split_range(a, s / a.score_parts);
+    {
+        const int i = s % a.score_parts, t0 = sr.tiles * i / a.score_parts;
+        sr = {sr.first + t0, sr.tiles * (i + 1) / a.score_parts - t0};
+    }
     const int64_t row = (int64_t)bh * a.Nq + min(qt * kQueryTile + wave * kQw + q, a.Nq - 1);
 
     const TileLoader loader(a, bh, sr.first, wave, lane);
@@ -1045,7 +1053,8 @@ __global__ __launch_bounds__(kThreads, 2) void split_scores_kernel(AttnArgs a) {
         if (j + 2 >= sr.tiles) break;
     }
     x = max_with_other_half(x);
-    if (h == 0) a.run_max[(((int64_t)bh * a.qtiles + qt) * a.nsplit + s) * kQueryTile + wave * kQw + q] = x;
+    if (h == 0)
+        a.run_max[(((int64_t)bh * a.qtiles + qt) * a.nsplit * a.score_parts + s) * kQueryTile + wave * kQw + q] = x;
 }
 
 // One workgroup per 32 query rows (a wave's of the main pass), wave n for
@@ -1232,12 +1241,12 @@ hipError_t launch_tile_scales(const uint8_t* ks, const uint8_t* vs, uint8_t* out
 // the division costs.  In tenths of a microsecond, measured: a tile takes 11
 // with one workgroup per CU, and 17 plus 4 for its scores with two, as the
 // divided passes run (512 workgroups); the score pass, the partial results
-// (33 MB written and read at 512 workgroups) and the combination cost 160.
+// (34 MB written and read at 512 workgroups) and the combination cost 160.
 // Required is a tenth less than the undivided time.  Runs have at least four
 // tiles: shorter ones cost more in partial results than they gain (70 tiles, 4
 // workgroups: 36 us in 17 runs, 40 in 35).  Both sides of the line (forward,
 // uos_pnq): 64 workgroups x 64 tiles, 8 runs, 79 -> 49 us; 48 x 929, 10 runs,
-// 1290 -> 574; undivided stay 60 x 20 (34.8, divided 37.9) and 160 x 32 (48.0,
+// 1290 -> 574 (550 with the scores in parts); undivided stay 60 x 20 (34.8, divided 37.9) and 160 x 32 (48.0,
 // in 3 runs 54.3); two runs gain nothing at any length (224 x 32: 50 -> 63).
 int key_splits(int64_t BH, int64_t Nq, int64_t Nkv) {
     const int64_t wgs = BH * ((Nq + kQueryTile - 1) / kQueryTile), tiles = (Nkv + kKvTile - 1) / kKvTile;
@@ -1272,7 +1281,7 @@ static hipError_t launch_attention_q(const AttnArgs& a, int mode, dim3 grid, hip
         return hipGetLastError();
     }
     const int tiles = a.total_tiles / a.nsplit;  // (head, query tile)
-    const dim3 sgrid((unsigned)(8 * ((tiles * (a.nsplit - 1) + 7) / 8)));
+    const dim3 sgrid((unsigned)(8 * ((tiles * (a.nsplit - 1) * a.score_parts + 7) / 8)));
     if (mode == 0)
         split_scores_kernel<kRuleOcp, kQraw><<<sgrid, kThreads, 0, stream>>>(a);
     else

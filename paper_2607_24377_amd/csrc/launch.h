@@ -65,7 +65,8 @@ struct AttnArgs {
     int per_xcd;
     int nchunks;        // resident kernel: workgroups per (batch, head)
     int nsplit;         // runs the keys of a head are divided into (1: not divided), and their workspace:
-    float* run_max;     // [BH, qtiles, nsplit, 128]: largest score of a run
+    int score_parts;    // parts of a run in the pass over the scores
+    float* run_max;     // [BH, qtiles, nsplit * score_parts, 128]: largest score of a part
     float2* part_ml;    // [BH, qtiles, nsplit, 128]: m and l after a run
     float4* part_o;     // [BH, qtiles, nsplit, 4 waves, 16, 64 lanes]: O~ of a run
 };
@@ -75,7 +76,8 @@ struct AttnArgs {
 int key_splits(int64_t BH, int64_t Nq, int64_t Nkv);
 // Workspace of a divided call: at most kMaxSplitWorkgroups workgroups' worth.
 constexpr int kMaxSplitWorkgroups = 512;
-constexpr size_t kSplitBytesPerWorkgroup = 128 * (128 * 4 + 8 + 4);
+constexpr int kScoreParts = 4;  // at most
+constexpr size_t kSplitBytesPerWorkgroup = 128 * (128 * 4 + 8 + 4 * kScoreParts);
 inline size_t split_bytes(int64_t BH, int64_t Nq, int nsplit) {
     return nsplit <= 1 ? 0 : (size_t)(BH * ((Nq + kQueryTile - 1) / kQueryTile) * nsplit) * kSplitBytesPerWorkgroup;
 }

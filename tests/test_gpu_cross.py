@@ -115,7 +115,7 @@ def test_resident_staged_stores_several_query_tiles(mx):
 # few query tiles over many keys: the keys are divided into runs that several
 # workgroups take (the last case: one tile less than the shortest divided one)
 @pytest.mark.parametrize("B,H,Nq,Nkv", [(1, 1, 130, 3073), (2, 2, 37, 8951), (1, 3, 300, 6400),
-                                        (1, 5, 1280, 9000), (1, 1, 130, 3072)])
+                                        (1, 5, 1280, 9000), (1, 20, 1000, 8001), (1, 1, 130, 3072)])
 def test_divided_keys(mx, B, H, Nq, Nkv):
     w = inputs.Workload(73, f"divided_{B}x{H}x{Nq}x{Nkv}", B, H, Nq, 128, "cross", Nkv=Nkv)
     for mode in MODES:
