@@ -400,146 +400,6 @@ __device__ __forceinline__ void tail_table(float* tail, int N, int tid) {
     }
 }
 
-// One KV tile of Algorithm 2 for the wave's 32 query rows, read from the LDS
-// stage at `st`: S^T = K^ Q^T, the online-softmax update of (m, l), P^ and
-// O~^T += V^T P^T.  Reads LDS only; the caller owns loads and barriers.
-// kFirst: the row's first tile, which sets m, l and O~ instead of updating
-// them (the rescale by alpha = 0 of a zero O~ and l is skipped, and the first
-// products accumulate onto zero), so they need no initial values.
-template <int kRule, bool kPnq, bool kFirst = false>
-__device__ __forceinline__ void attend_tile(const uint8_t* st, const LaneOff& lo, const float* tail, int tile, int N,
-                                            int h, const QOperands& qo, const v8i& sel, float& m, RowSum& rs,
-                                            v16f (&O)[4]) {
-    const float cl = 0.12751743082459868f;  // fp32(log2(e) / sqrt(128))
-    const v8i& qB0 = qo.b0;
-    const v8i& qB1 = qo.b1;
-    const int qS0 = qo.s0, qS1 = qo.s1;
-    const uint2 ksb = ld64<kKsOff>(st, lo.sc);
-    const uint2 vsb = ld64<kVsOff>(st, lo.sc);
-
-    // ---- K^ operands for the 8 S products (chunk c, tile j, half hf):
-    // row 64 c + 32 j + q
-    v8i kop[2][2][2];
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-        kop[c][0][0] = fp4_v(ld128<kKcOff + 0 * 2048>(st + 4096 * c, lo.lo));
-        kop[c][0][1] = fp4_v(ld128<kKcOff + 0 * 2048>(st + 4096 * c, lo.hi));
-        kop[c][1][0] = fp4_v(ld128<kKcOff + 1 * 2048>(st + 4096 * c, lo.lo));
-        kop[c][1][1] = fp4_v(ld128<kKcOff + 1 * 2048>(st + 4096 * c, lo.hi));
-    }
-
-    // ---- S^T = K^ Q^T: S[c][j][i] is key 64c + 32h + 16j + i of the tile.  In
-    // the ragged last tile the products accumulate onto -inf for keys past the
-    // end (and onto 0 for the others, as elsewhere), read from the table of
-    // tail_table: masking takes no vector instruction.  A second chunk with no
-    // key at all is left out.
-    v16f S[2][2];
-    auto products = [&](int c, int j, v16f acc) {
-        const int sreg = c == 0 ? (int)ksb.x : (int)ksb.y;
-        if (j == 0) {
-            acc = mfma_fp4<0>(kop[c][j][0], qB0, acc, sreg, qS0);
-            return mfma_fp4<1>(kop[c][j][1], qB1, acc, sreg, qS1);
-        }
-        acc = mfma_fp4<2>(kop[c][j][0], qB0, acc, sreg, qS0);
-        return mfma_fp4<3>(kop[c][j][1], qB1, acc, sreg, qS1);
-    };
-    const int left = N - tile * 128;  // keys from the tile's first on
-    const bool two = left > 64;       // the second chunk has keys
-    if (left >= 128) {
-        const v16f zero = {};
-#pragma unroll
-        for (int c = 0; c < 2; c++)
-#pragma unroll
-            for (int j = 0; j < 2; j++) S[c][j] = products(c, j, zero);
-    } else {
-        const v16f* tab = reinterpret_cast<const v16f*>(tail) + 4 * h;
-#pragma unroll
-        for (int j = 0; j < 2; j++) S[0][j] = products(0, j, tab[j]);
-#pragma unroll
-        for (int j = 0; j < 2; j++) S[1][j] = two ? products(1, j, tab[2 + j]) : tab[2 + j];
-    }
-
-    // ---- V^ operands for the PV products (read now, used after softmax):
-    // row (channel) 32 n + q
-    v8i vop[4][2];
-#pragma unroll
-    for (int n = 0; n < 4; n++) {
-        vop[n][0] = fp4_v(ld128<kVcOff>(st + 2048 * n, lo.lo));
-        vop[n][1] = fp4_v(ld128<kVcOff>(st + 2048 * n, lo.hi));
-    }
-
-    // ---- running maximum: the block maxima (one P~ block per lane and
-    // chunk), the tile maximum of the row across the lane pair
-    float bmax[2];
-#pragma unroll
-    for (int c = 0; c < 2; c++) bmax[c] = block_max32(S[c][0], S[c][1]);
-    float rmax = max_with_other_half(max2f(bmax[0], bmax[1]));
-    const float m_new = kFirst ? mul_rd(cl, rmax) : max2f(m, mul_rd(cl, rmax));
-    const float alpha = kFirst ? 0.f : __builtin_amdgcn_exp2f(m - m_new);  // 0 on the first tile
-    m = m_new;
-
-    // ---- O~^T rescale, then per 64-key chunk: P~ -> P^ and that chunk's PV
-    // products (so chunk 0's products run under chunk 1's softmax)
-    if (!kFirst && __any(alpha != 1.f)) {
-#pragma unroll
-        for (int n = 0; n < 4; n++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) O[n][i] *= alpha;
-        if (kPnq) {
-            // lane q < 16 holds the sums of queries q and q + 16: the second
-            // takes alpha of lane q + 16 (row 1 of the first operand swaps
-            // with row 0 of the second)
-            const uint32_t ab = __builtin_bit_cast(uint32_t, alpha);
-            const auto r = __builtin_amdgcn_permlane16_swap(ab, ab, false, false);
-            rs.L[0] *= alpha;
-            rs.L[1] *= __builtin_bit_cast(float, (uint32_t)r[1]);
-        }
-    }
-    float lsum = 0.f;
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-        if (c == 1 && !two) break;
-        const float mb = __builtin_amdgcn_exp2f(__builtin_fmaf(bmax[c], cl, -m_new));
-        const uint32_t sbits = p_scale_bits<kRule>(__builtin_bit_cast(uint32_t, mb));
-        const float sf = __builtin_bit_cast(float, sbits);
-        const int psc = (int)(sbits >> 23);
-        uint32_t w[4];
-#pragma unroll
-        for (int n = 0; n < 32; n += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[c][n >> 4][n & 15], cl, -m_new));
-            const float p1 =
-                __builtin_amdgcn_exp2f(__builtin_fmaf(S[c][(n + 1) >> 4][(n + 1) & 15], cl, -m_new));
-            if (!kPnq) lsum += p0 + p1;
-            const uint32_t prev = (n & 7) == 0 ? __builtin_bit_cast(uint32_t, p0) : w[n >> 3];
-            w[n >> 3] = cvt_fp4x2(prev, p0, p1, sf, (n & 7) >> 1);
-        }
-        const v8i P = fp4_operand(make_uint4(w[0], w[1], w[2], w[3]));
-        if (kFirst && c == 0) {
-            const v16f zero = {};
-            if (kPnq) rs.L = mfma16_fp4(sel, P, v4f{0.f, 0.f, 0.f, 0.f}, 127, psc);
-            O[0] = mfma_fp4<0>(vop[0][0], P, zero, (int)vsb.x, psc);
-            O[1] = mfma_fp4<2>(vop[1][0], P, zero, (int)vsb.x, psc);
-            O[2] = mfma_fp4<0>(vop[2][0], P, zero, (int)vsb.y, psc);
-            O[3] = mfma_fp4<2>(vop[3][0], P, zero, (int)vsb.y, psc);
-            continue;
-        }
-        if (kPnq) rs.L = mfma16_fp4(sel, P, rs.L, 127, psc);
-        // scale byte 2 (n & 1) + c of the register of channel rows 32 n
-        if (c == 0) {
-            O[0] = mfma_fp4<0>(vop[0][0], P, O[0], (int)vsb.x, psc);
-            O[1] = mfma_fp4<2>(vop[1][0], P, O[1], (int)vsb.x, psc);
-            O[2] = mfma_fp4<0>(vop[2][0], P, O[2], (int)vsb.y, psc);
-            O[3] = mfma_fp4<2>(vop[3][0], P, O[3], (int)vsb.y, psc);
-        } else {
-            O[0] = mfma_fp4<1>(vop[0][1], P, O[0], (int)vsb.x, psc);
-            O[1] = mfma_fp4<3>(vop[1][1], P, O[1], (int)vsb.x, psc);
-            O[2] = mfma_fp4<1>(vop[2][1], P, O[2], (int)vsb.y, psc);
-            O[3] = mfma_fp4<3>(vop[3][1], P, O[3], (int)vsb.y, psc);
-        }
-    }
-    if (!kPnq) rs.l = kFirst ? lsum : alpha * rs.l + lsum;
-}
-
 // O = O~ / l rounded to bf16 (Eq. online_attention_output), as O~ times the
 // fp32 reciprocal of l; lane (q, h) holds channels 32 n + 8 g + 4 h + (0..3)
 // of its query row.
@@ -634,17 +494,16 @@ __device__ __forceinline__ void store_rows(const AttnArgs& a, int64_t rowbase, i
 }
 
 // ---------------------------------------------------------------------------
-// Long key sequences: the same tile computation, software-pipelined: the
-// score products of tile j + 1 are issued during the softmax of tile j (each
-// as soon as the score registers it overwrites have been consumed) and the
-// second PV chunk of a tile is deferred into the next one, so that no wave
-// waits for its own score products before its maximum and no LDS read sits
-// right before the product that consumes it.  On video720p this runs as fast
-// as a two-stage loop that issues each tile's score products as one group and
-// waits for them (the vector-ALU issue rate of the softmax bounds both), with
-// results identical bit for bit; it is kept because its LDS reads are
-// ordinary loads (see below) and its tail masking holds no per-score masks in
-// scalar registers.
+// Long key sequences: the tile computation software-pipelined: the score
+// products of tile j + 1 are issued during the softmax of tile j (each as soon
+// as the score registers it overwrites have been consumed) and the second PV
+// chunk of a tile is deferred into the next one, so that no wave waits for its
+// own score products before its maximum and no LDS read sits right before the
+// product that consumes it.  At 720p (40 heads x 75600^2, uos_pnq) a wave-tile
+// takes 241 vector instructions and 1714 cycles, the vector ALU issuing in 84 %
+// of them, at the 2.18 GHz that the chip holds under this load; a loop without
+// this overlap at three waves per SIMD was 1.5 % slower, one barrier per two
+// tiles (68 KiB of LDS) within 1 %.
 //
 // Per KV tile j of a wave (stage s = j mod 3 holds tile j's K^, V^ and scales):
 //   A  read tile j-1's chunk-1 V^ operands; block and row maxima of S(j),
@@ -657,9 +516,9 @@ __device__ __forceinline__ void store_rows(const AttnArgs& a, int64_t rowbase, i
 //   C  the rest of chunk 0, its products with V^ threaded through chunk 1's
 //      softmax, and the score products of tile j+1, each issued as soon as
 //      the score registers it overwrites have been consumed.
-// Every accumulator still receives its terms in the same order as in
-// attend_tile (O~: chunk 0 then chunk 1 of each tile, then the next tile's
-// rescale), so the results are identical.
+// Every accumulator receives its terms in the order of the unoverlapped loop
+// (O~: chunk 0 then chunk 1 of each tile, then the next tile's rescale), so the
+// results are the same.
 //
 // The three stages are separate LDS arrays read by ordinary loads, so the
 // compiler orders them against the buffer-to-LDS copies by their arrays
@@ -687,10 +546,10 @@ __device__ __forceinline__ KOperands k_operands(const uint8_t* stage, const Lane
 // The two score products of S[c][jj] (keys 64 c + 32 h + 16 jj + i of the
 // tile).
 template <int kC, int kJ>
-__device__ __forceinline__ v16f score_pair(const KOperands& k, const QOperands& qo, uint2 ksb) {
+__device__ __forceinline__ v16f score_pair(const KOperands& k, const QOperands& qo, uint2 ksb,
+                                           const v16f& init = v16f{}) {
     const int sreg = kC == 0 ? (int)ksb.x : (int)ksb.y;
-    const v16f zero = {};
-    v16f acc = mfma_fp4<2 * kJ>(fp4_v(k.lo[kC][kJ]), qo.b0, zero, sreg, qo.s0);
+    v16f acc = mfma_fp4<2 * kJ>(fp4_v(k.lo[kC][kJ]), qo.b0, init, sreg, qo.s0);
     return mfma_fp4<2 * kJ + 1>(fp4_v(k.hi[kC][kJ]), qo.b1, acc, sreg, qo.s1);
 }
 
@@ -1096,18 +955,138 @@ __global__ __launch_bounds__(256) void split_combine_kernel(AttnArgs a) {
     }
 }
 
+// The same offsets, unknown to the compiler: what is read at them is read past
+// this point, not hoisted out of the loop over query tiles (K^ and V^ are the
+// same in each) or ahead by whole tiles.
+__device__ __forceinline__ LaneOff read_here(LaneOff lo) {
+    asm volatile("" : "+v"(lo.sc), "+v"(lo.lo), "+v"(lo.hi));
+    return lo;
+}
+
+// ---------------------------------------------------------------------------
+// One KV tile of a query tile whose head's tiles are all in LDS: the steps of
+// pipe_tile without loads and barriers.  `st` is the tile's stage; the next
+// tile's lies behind it, the previous one's before it.
+//   kFirst     the row's first tile, which sets m, l and O~ instead of updating
+//              them
+//   kLast      no next tile to score; `two` says whether its second chunk has
+//              any key (every other tile is whole)
+//   kNextTail  the next tile is the last one: its scores start from the table
+//              `tail` (tail_table; all zero if the tile is whole)
+template <int kRule, bool kPnq, bool kFirst, bool kLast, bool kNextTail>
+__device__ __forceinline__ void resident_tile(const uint8_t* st, const LaneOff& lane_offsets, const float* tail,
+                                              bool two, int h, const QOperands& qo, const v8i& sel, PipeState& ps) {
+    const LaneOff lo = read_here(lane_offsets);
+    // ---- A: the previous tile's chunk-1 V^ operands, the maxima, alpha
+    VOperands vprev;
+    if constexpr (!kFirst) vprev = v_operands<1>(st - kStageBytes, lo);
+    float bmax[2];
+    bmax[0] = block_max32(ps.S[0][0], ps.S[0][1]);
+    bmax[1] = -__builtin_inff();
+    if (!kLast || two) bmax[1] = block_max32(ps.S[1][0], ps.S[1][1]);
+    const float rmax = max_with_other_half(max2f(bmax[0], bmax[1]));
+    const float m_old = ps.m;
+    // (some row of 32 rises on nearly every tile of a short sequence)
+    ps.m = mul_rd(0.12751743082459868f, rmax);
+    float alpha = 1.f;
+    if constexpr (!kFirst) {
+        ps.m = max2f(m_old, ps.m);
+        alpha = __builtin_amdgcn_exp2f(m_old - ps.m);
+    }
+    const float m_new = ps.m;
+
+    // ---- B: the LDS reads of the rest of the tile; the previous tile's
+    // deferred products under the first half of chunk 0
+    const uint2 vsb = ld64<kVsOff>(st, lo.sc);
+    const VOperands vc0 = v_operands<0>(st, lo);
+    uint2 ksb = make_uint2(0u, 0u);
+    KOperands kn;
+    if constexpr (!kLast) {
+        ksb = ld64<kKsOff>(st + kStageBytes, lo.sc);
+        kn = k_operands(st + kStageBytes, lo);
+    }
+    const v16f* tab = reinterpret_cast<const v16f*>(tail) + 4 * h;
+    if constexpr (!kFirst) pv_chunk<kPnq, 1>(vprev, ps.P1, ps.psc1, ps.vsb1, sel, ps.rs, ps.O);
+    float lsum = 0.f;
+    uint32_t w0[4], w1[4];
+    const uint32_t sb0 = block_scale<kRule>(bmax[0], m_new);
+    const float sf0 = __builtin_bit_cast(float, sb0);
+    softmax_half<kRule, kPnq, 0>(ps.S[0][0], m_new, sf0, w0, lsum);
+    if constexpr (!kLast) {
+        ps.S[0][0] = score_pair<0, 0>(kn, qo, ksb, kNextTail ? tab[0] : v16f{});
+        pin_here(ps.S[0][0][0], w0[0], w0[1], lsum);
+    }
+    if constexpr (!kFirst) {
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+            for (int n = 0; n < 4; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) ps.O[n][i] *= alpha;
+            if (kPnq) {
+                const uint32_t ab = __builtin_bit_cast(uint32_t, alpha);
+                const auto r = __builtin_amdgcn_permlane16_swap(ab, ab, false, false);
+                ps.rs.L[0] *= alpha;
+                ps.rs.L[1] *= __builtin_bit_cast(float, (uint32_t)r[1]);
+            }
+        }
+    }
+
+    // ---- C: the rest of chunk 0 and its products, chunk 1, the next scores
+    softmax_half<kRule, kPnq, 1>(ps.S[0][1], m_new, sf0, w0, lsum);
+    if constexpr (!kLast) ps.S[0][1] = score_pair<0, 1>(kn, qo, ksb, kNextTail ? tab[1] : v16f{});
+    pin_here(w0[2], w0[3], lsum);
+    const v8i P0 = fp4_operand(make_uint4(w0[0], w0[1], w0[2], w0[3]));
+    const int psc0 = (int)(sb0 >> 23);
+    if constexpr (kFirst) {
+        const v16f zero = {};
+        if (kPnq) ps.rs.L = mfma16_fp4(sel, P0, v4f{0.f, 0.f, 0.f, 0.f}, 127, psc0);
+        ps.O[0] = mfma_fp4<0>(fp4_v(vc0.v[0]), P0, zero, (int)vsb.x, psc0);
+        ps.O[1] = mfma_fp4<2>(fp4_v(vc0.v[1]), P0, zero, (int)vsb.x, psc0);
+        ps.O[2] = mfma_fp4<0>(fp4_v(vc0.v[2]), P0, zero, (int)vsb.y, psc0);
+        ps.O[3] = mfma_fp4<2>(fp4_v(vc0.v[3]), P0, zero, (int)vsb.y, psc0);
+    } else {
+        pv_chunk<kPnq, 0>(vc0, P0, psc0, vsb, sel, ps.rs, ps.O);
+    }
+    ps.P1 = v8i{};
+    ps.psc1 = 127;
+    if (!kLast || two) {
+        const uint32_t sb1 = block_scale<kRule>(bmax[1], m_new);
+        const float sf1 = __builtin_bit_cast(float, sb1);
+        softmax_half<kRule, kPnq, 0>(ps.S[1][0], m_new, sf1, w1, lsum);
+        if constexpr (!kLast) {
+            ps.S[1][0] = score_pair<1, 0>(kn, qo, ksb, kNextTail ? tab[2] : v16f{});
+            pin_here(ps.S[1][0][0], w1[0], w1[1], lsum);
+        }
+        softmax_half<kRule, kPnq, 1>(ps.S[1][1], m_new, sf1, w1, lsum);
+        if constexpr (!kLast) {
+            ps.S[1][1] = score_pair<1, 1>(kn, qo, ksb, kNextTail ? tab[3] : v16f{});
+            pin_here(lsum, ps.S[0][1][0], ps.S[1][1][0], ps.O[0][0], ps.O[1][0], ps.O[2][0], ps.O[3][0]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ps.P1 = fp4_operand(make_uint4(w1[0], w1[1], w1[2], w1[3]));
+        ps.psc1 = (int)(sb1 >> 23);
+    }
+    ps.vsb1 = vsb;
+    if (!kPnq) ps.rs.l = kFirst ? lsum : alpha * ps.rs.l + lsum;
+}
+
 // Short key sequences (cross-attention over a text context, at most
 // kResidentKeys keys): the workgroup copies all of the head's K^ and V^ tiles
 // into LDS once and then runs several query tiles of that head against them,
 // with no per-tile loads or barriers; each query tile is the same computation
-// as in the streaming kernel.
-constexpr int kResidentTiles = kResidentKeys / 128;
-static_assert(kStagedStoreMaxTiles < kResidentTiles && kWaves * kOutStageBytes <= kStageBytes,
-              "the output staging buffers fit in an unused tile slot");
+// as in the streaming kernel, with kTiles = 1 to 4 key tiles in a row (as a
+// loop over a run-time count the 128 registers of scores and O~ met at every
+// branch and spilled).  512 keys: vector issue busy 77 % and 0.45 ms at 40 heads
+// x 75600 queries, of which reading Q and writing O takes 0.30; scoring the next
+// tile under the softmax gained 1 to 6 % (5 heads x 20000 queries 29.0 -> 27.6
+// us) over issuing each tile's products as one group.
+static_assert(kResidentKeys == 4 * 128, "one instantiation per number of key tiles");
 
-template <int kRule, bool kPnq, bool kQraw>
+template <int kRule, bool kPnq, bool kQraw, int kTiles>
 __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kResidentTiles * kStageBytes];
+    // up to kStagedStoreMaxTiles the output rows are staged behind the tiles
+    constexpr bool staged = kTiles <= kStagedStoreMaxTiles;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kTiles * kStageBytes + (staged ? kWaves * kOutStageBytes : 0)];
     __shared__ __attribute__((aligned(64))) float tail[kTailFloats];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1125,13 +1104,10 @@ __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArg
     const int N = a.N;
     const int Nq = a.Nq;
     const int64_t rowbase = (int64_t)bh * Nq;
-    const int ntiles = (N + 127) / 128;
-    // staging goes to the first unused tile slot
-    const bool staged = ntiles <= kStagedStoreMaxTiles;
-    uint8_t* const ostage = lds + ntiles * kStageBytes + wave * kOutStageBytes;
+    uint8_t* const ostage = lds + (staged ? kTiles : 0) * kStageBytes + wave * kOutStageBytes;
 
     const TileLoader loader(a, bh, 0, wave, lane);
-    for (int t = 0; t < ntiles; t++) loader.load(lds + t * kStageBytes, t);
+    for (int t = 0; t < kTiles; t++) loader.load(lds + t * kStageBytes, t);
 
     const v8i sel = row_sum_selector(lane);
     const LaneOff lo = lane_off(q, h, lane);
@@ -1166,22 +1142,36 @@ __global__ __launch_bounds__(kThreads, 2) void attention_resident_kernel(AttnArg
         }
     };
     QOperands qo = operands(fetch(qt0));
+    const bool two = N - (kTiles - 1) * 128 > 64;
+    PipeState ps;  // set by a query tile's first tile
 
     for (int qt = qt0; qt < qt1; qt++) {
         const int qi = qt * kQueryTile + wave * kQw + q;
+        {
+            const LaneOff lh = read_here(lo);
+            const uint2 ksb = ld64<kKsOff>(lds, lh.sc);
+            const KOperands k = k_operands(lds, lh);
+            const v16f* tab = reinterpret_cast<const v16f*>(tail) + 4 * h;
+            ps.S[0][0] = score_pair<0, 0>(k, qo, ksb, kTiles == 1 ? tab[0] : v16f{});
+            ps.S[0][1] = score_pair<0, 1>(k, qo, ksb, kTiles == 1 ? tab[1] : v16f{});
+            ps.S[1][0] = score_pair<1, 0>(k, qo, ksb, kTiles == 1 ? tab[2] : v16f{});
+            ps.S[1][1] = score_pair<1, 1>(k, qo, ksb, kTiles == 1 ? tab[3] : v16f{});
+        }
+        if constexpr (kTiles > 1)
+            resident_tile<kRule, kPnq, true, false, kTiles == 2>(lds, lo, tail, true, h, qo, sel, ps);
+        if constexpr (kTiles > 2)
+            resident_tile<kRule, kPnq, false, false, kTiles == 3>(lds + kStageBytes, lo, tail, true, h, qo, sel, ps);
+        if constexpr (kTiles > 3)
+            resident_tile<kRule, kPnq, false, false, true>(lds + 2 * kStageBytes, lo, tail, true, h, qo, sel, ps);
+        const uint8_t* const st = lds + (kTiles - 1) * kStageBytes;
         // the last query tile fetches itself again: no branch around the loads
         const QFetch next = fetch(min(qt + 1, qt1 - 1));
-
-        // set by the first tile (N >= 1, so there is one)
-        float m;
-        RowSum rs;
-        v16f O[4];
-        attend_tile<kRule, kPnq, true>(lds, lo, tail, 0, N, h, qo, sel, m, rs, O);
-        for (int tile = 1; tile < ntiles; tile++)
-            attend_tile<kRule, kPnq>(lds + tile * kStageBytes, lo, tail, tile, N, h, qo, sel, m, rs, O);
+        resident_tile<kRule, kPnq, kTiles == 1, true, false>(st, lo, tail, two, h, qo, sel, ps);
+        // the last tile's chunk-1 products
+        pv_chunk<kPnq, 1>(v_operands<1>(st, read_here(lo)), ps.P1, ps.psc1, ps.vsb1, sel, ps.rs, ps.O);
 
         const QOperands qn = operands(next);
-        store_rows<kPnq>(a, rowbase, qi, q, h, lane, ostage, staged, rs, O);
+        store_rows<kPnq>(a, rowbase, qi, q, h, lane, ostage, staged, ps.rs, ps.O);
         qo = qn;
     }
 }
@@ -1266,13 +1256,23 @@ static void launch_pipelined(const AttnArgs& a, int mode, dim3 grid, hipStream_t
     }
 }
 
+template <bool kQraw, int kTiles>
+static void launch_resident(const AttnArgs& a, int mode, dim3 grid, hipStream_t stream) {
+    switch (mode) {
+        case 0: attention_resident_kernel<kRuleOcp, false, kQraw, kTiles><<<grid, kThreads, 0, stream>>>(a); break;
+        case 1: attention_resident_kernel<kRuleUos, false, kQraw, kTiles><<<grid, kThreads, 0, stream>>>(a); break;
+        default: attention_resident_kernel<kRuleUos, true, kQraw, kTiles><<<grid, kThreads, 0, stream>>>(a); break;
+    }
+}
+
 template <bool kQraw>
 static hipError_t launch_attention_q(const AttnArgs& a, int mode, dim3 grid, hipStream_t stream) {
     if (a.N <= kResidentKeys) {
-        switch (mode) {
-            case 0: attention_resident_kernel<kRuleOcp, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
-            case 1: attention_resident_kernel<kRuleUos, false, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
-            default: attention_resident_kernel<kRuleUos, true, kQraw><<<grid, kThreads, 0, stream>>>(a); break;
+        switch ((a.N + 127) / 128) {
+            case 1: launch_resident<kQraw, 1>(a, mode, grid, stream); break;
+            case 2: launch_resident<kQraw, 2>(a, mode, grid, stream); break;
+            case 3: launch_resident<kQraw, 3>(a, mode, grid, stream); break;
+            default: launch_resident<kQraw, 4>(a, mode, grid, stream); break;
         }
         return hipGetLastError();
     }
