@@ -25,22 +25,25 @@
 // the same p they classify every entry identically and their fp64 sums differ
 // only in the order of additions.
 //
-// Row sums.  m and L of a row are formed in runs of kRunTiles key tiles
-// (RowMax: an online maximum and sum per lane, the two lanes of a row merged
-// at the end of the run) that are merged in key order.  A launch with many row
-// tiles walks the runs in one workgroup per row tile (attn_rows_kernel); one
-// with few, which would leave most of the chip idle, gives every run its own
-// workgroup in two passes with a merge between them (rows_partial_kernel,
-// rows_merge_kernel, rows_write_kernel).  Both form m, L and p from the same
-// operations in the same order, bit for bit.
+// Row sums.  Each of a row's two lanes walks its share of the keys (every other
+// four) with an online maximum and one chain of fp32 additions, and the two are
+// merged at the end (row_max).  The order is part of the result: the quantized
+// statistics jump where an entry's block maximum crosses 7.25/8 of a power of
+// two, so another association of L (4e-5 at 32760 keys, where the chain rounds
+// small terms away) moves whole entries of P^, and a row by up to 0.3.  L is
+// therefore not divided over workgroups.  p given m and L is: a launch with few
+// row tiles, which would leave most of the chip idle, forms m and L in one
+// workgroup per row tile (rows_norm_kernel) and p in one per 8 key tiles
+// (rows_write_kernel).  Both ways form m, L and p from the same operations in
+// the same order, bit for bit.
 //
-// What bounds them (one MI355X): the fused diagnostic vector issue (89 % busy;
-// about 30 vector instructions per entry over the two passes: 40 heads x 4096^2
-// entries in 0.72 ms; with every class summed per entry in fp64 behind compares
-// and selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries HBM
-// (K read twice, P written: 0.08 + 0.25 ms; with one workgroup per row tile
-// 2.9 ms, 40 workgroups on 256 CUs) and their diagnostic again vector issue
-// (0.20 ms = 3.3 TB/s of P; before 0.24 ms).
+// What bounds them (one MI355X): the fused diagnostic vector issue (about 30
+// vector instructions per entry over the two passes: 40 heads x 4096^2 entries
+// in 0.75 ms; with every class summed per entry in fp64 behind compares and
+// selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries the chain
+// of L in 40 workgroups, one wave per SIMD (@NORM ms), then HBM (P written, 0.25
+// ms; both passes in one workgroup per row tile 2.9 ms), and their diagnostic
+// again vector issue (0.20 ms = 3.3 TB/s of P; before 0.24 ms).
 #include <cmath>
 
 #include "device_common.h"
@@ -54,18 +57,19 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kRowsPerWg = 128;  // query rows per workgroup (4 waves x 32)
 constexpr int kKeyTile = 128;    // keys staged in LDS per step (32 KiB)
-constexpr int kRunTiles = 8;     // key tiles per run
+constexpr int kRunTiles = 8;     // key tiles per workgroup of rows_write_kernel
 constexpr float kNegBig = -3.0e38f;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 // Copies keys [tile * 128, tile * 128 + 128) of one head straight into LDS
 // (buffer loads to LDS; the buffer's range check reads zeros past Nkv).  LDS
-// row 64 c + 32 j + r holds key 64 c + 32 ((r >> 2) & 1) + 16 j + 4 (r >> 3) +
-// (r & 3), so that lane (query, h) finds keys 32 h .. 32 h + 31 of the chunk c
-// in the accumulators of its two score products; the 16-byte slot of a row is
-// XOR-ed with the row, so 16 consecutive rows read at one slot hit 16 bank
-// groups.
+// row 64 c + 32 j + r holds, with kBlocks, key 64 c + 32 ((r >> 2) & 1) + 16 j +
+// 4 (r >> 3) + (r & 3), so that lane (query, h) finds keys 32 h .. 32 h + 31 of
+// the chunk c in the accumulators of its two score products, and otherwise key
+// 64 c + 32 j + r.  The 16-byte slot of a row is XOR-ed with the row, so 16
+// consecutive rows read at one slot hit 16 bank groups.
+template <bool kBlocks>
 struct KeyStage {
     const uint8_t* kh;
     int Nkv, wave;
@@ -74,11 +78,11 @@ struct KeyStage {
     __device__ __forceinline__ KeyStage(const uint16_t* k, int64_t bh, int nkv, int wave_, int lane)
         : kh(reinterpret_cast<const uint8_t*>(k) + bh * (int64_t)nkv * 256), Nkv(nkv), wave(wave_) {
         const int x = lane >> 4;  // row of a load's four
-        off = (uint32_t)((64 * (wave >> 1) + 16 * (wave & 1) + x) * 256 + ((lane & 15) ^ x) * 16);
+        off = (uint32_t)((64 * (wave >> 1) + (kBlocks ? 16 : 32) * (wave & 1) + x) * 256 + ((lane & 15) ^ x) * 16);
     }
 
     // wave w copies LDS rows 32 w .. 32 w + 31 (A-rows of product (c, j) = (w >> 1, w & 1)), four per
-    // load: row 4 i + x is key 32 (i & 1) + 4 (i >> 1) + x further on, its slots XOR-ed by 4 (i & 3) + x
+    // load: row 4 i + x is key 32 (i & 1) + 4 (i >> 1) + x or 4 i + x further on, its slots XOR-ed by 4 (i & 3) + x
     __device__ __forceinline__ void load(uint8_t* lds, int tile_) const {
         const int tile = __builtin_amdgcn_readfirstlane(tile_);
         const int64_t left = ((int64_t)Nkv - (int64_t)tile * kKeyTile) * 256;
@@ -91,7 +95,7 @@ struct KeyStage {
         for (int i = 0; i < 8; i++)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rs, (lds_ptr_t)(lds + wave * 8192 + i * 1024), 16,
-                (int)((base ^ (64 * (i & 3))) + (32 * (i & 1) + 4 * (i >> 1)) * 256), 0, 0, 0);
+                (int)((base ^ (64 * (i & 3))) + (kBlocks ? 32 * (i & 1) + 4 * (i >> 1) : 4 * i) * 256), 0, 0, 0);
     }
 };
 
@@ -112,9 +116,11 @@ __device__ __forceinline__ v16f scores_t(const bf16x8* qb, const uint8_t* lds, i
     return acc;
 }
 
-// The scores of the staged tile: sv[c][j][i] is the lane's key 64 c + 32 h +
-// 16 j + i, -inf past the end of the sequence.
+// The scores of the staged tile, -inf past the end of the sequence: sv[c][j][i]
+// is key 64 c + 32 h + 16 j + i with kBlocks, otherwise 64 c + 32 j + 8 (i >> 2)
+// + 4 h + (i & 3).
 typedef v16f TileScores[2][2];
+template <bool kBlocks>
 __device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds, int t, int Nkv, int col, int h,
                                             TileScores& sv) {
 #pragma unroll
@@ -122,14 +128,14 @@ __device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds
 #pragma unroll
         for (int j = 0; j < 2; j++) sv[c][j] = scores_t(qb, lds, 2 * c + j, col, h);
     if ((t + 1) * kKeyTile > Nkv) {
-        const int valid = Nkv - t * kKeyTile - 32 * h;
+        const int valid = Nkv - t * kKeyTile - (kBlocks ? 32 : 4) * h;
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
                 for (int i = 0; i < 16; i++)
-                    if (64 * c + 16 * j + i >= valid) sv[c][j][i] = -INFINITY;
+                    if (64 * c + (kBlocks ? 16 * j + i : 32 * j + 8 * (i >> 2) + (i & 3)) >= valid) sv[c][j][i] = -INFINITY;
     }
 }
 
@@ -138,8 +144,8 @@ __device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds
 // in registers; the work calls landed() once, where the copy should be through
 // (vmcnt counts stores too: before its stores, so that they are not waited for
 // at the next tile).
-template <typename Work>
-__device__ __forceinline__ void for_tiles(const bf16x8* qb, const KeyStage& ks, uint8_t* lds, int t0, int t1, int col,
+template <bool kBlocks, typename Work>
+__device__ __forceinline__ void for_tiles(const bf16x8* qb, const KeyStage<kBlocks>& ks, uint8_t* lds, int t0, int t1, int col,
                                           int h, const Work& work) {
     auto landed = [] { __builtin_amdgcn_s_waitcnt(0); };
     ks.load(lds, t0);
@@ -147,7 +153,7 @@ __device__ __forceinline__ void for_tiles(const bf16x8* qb, const KeyStage& ks, 
     for (int t = t0; t < t1; t++) {
         __syncthreads();  // tile t landed everywhere
         TileScores sv;
-        tile_scores(qb, lds, t, ks.Nkv, col, h, sv);
+        tile_scores<kBlocks>(qb, lds, t, ks.Nkv, col, h, sv);
         __syncthreads();  // and was read everywhere
         if (t + 1 < t1) ks.load(lds, t + 1);
         work(t, sv, landed);
@@ -164,51 +170,44 @@ __device__ __forceinline__ void load_queries(const SoftmaxRowsArgs& a, int64_t b
 // Scores are never NaN: the NaN-propagating maximum fuses into the 3-input form.
 __device__ __forceinline__ float max2f(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
-// Maximum and sum of a row's 2^(t - m), t = c s: (m, l) of a run, or of the
-// runs so far.
-struct RowMax {
-    float m, l;
+// A row's maximum m of t = c s, and 1 / L of its two lanes, which merge their
+// sums each with its own first: entry (key >> 2) & 1 belongs to that lane's keys.
+struct RowNorm {
+    float m, inv[2];
 };
-__device__ __forceinline__ RowMax merge(RowMax a, RowMax b) {
-    const float m = max2f(a.m, b.m);
-    const float bl = b.l * __builtin_amdgcn_exp2f(b.m - m);
-    return {m, __builtin_fmaf(a.l, __builtin_amdgcn_exp2f(a.m - m), bl)};
+
+// fp32(s c), not fused into a later addition.
+__device__ __forceinline__ float rounded_product(float s, float c) {
+#pragma clang fp contract(off)
+    return s * c;
 }
 
-// (m, l) of the row over tiles t0 .. t1 - 1 (t0 at the start of a run), the
-// same in both of the row's lanes.
-__device__ __forceinline__ RowMax row_max(const SoftmaxRowsArgs& a, const KeyStage& ks, const bf16x8* qb, uint8_t* lds,
-                                          int t0, int t1, int col, int h) {
-    RowMax total = {kNegBig, 0.f}, r = total;
-    for_tiles(qb, ks, lds, t0, t1, col, h, [&](int t, TileScores& sv, auto landed) {
+__device__ __forceinline__ RowNorm row_norm(const SoftmaxRowsArgs& a, int64_t bh, const bf16x8* qb, uint8_t* lds,
+                                            int wave, int lane, int col, int h) {
+    const KeyStage<false> ks(a.k, bh, a.Nkv, wave, lane);
+    float m = kNegBig, l = 0.f;
+    for_tiles<false>(qb, ks, lds, 0, (a.Nkv + kKeyTile - 1) / kKeyTile, col, h, [&](int, TileScores& sv, auto landed) {
+        float tm = sv[0][0][0];
 #pragma unroll
-        for (int c = 0; c < 2; c++) {
-            float x = sv[c][0][0], y = sv[c][1][0];
+        for (int i = 1; i < 63; i += 2)
+            tm = max2f(max2f(tm, sv[i >> 5][(i >> 4) & 1][i & 15]), sv[(i + 1) >> 5][((i + 1) >> 4) & 1][(i + 1) & 15]);
+        tm = max2f(tm, sv[1][1][15]);
+        // (a lane whose keys are all past the end keeps m: c tm = -inf)
+        const float mn = max2f(m, rounded_product(tm, a.c));
+        float acc = l * __builtin_amdgcn_exp2f(m - mn);
 #pragma unroll
-            for (int i = 1; i < 15; i += 2) {
-                x = max2f(max2f(x, sv[c][0][i]), sv[c][0][i + 1]);
-                y = max2f(max2f(y, sv[c][1][i]), sv[c][1][i + 1]);
-            }
-            // (a lane whose 32 keys are all past the end keeps m: c x = -inf)
-            const float mn = max2f(r.m, a.c * max2f(max2f(x, sv[c][0][15]), max2f(y, sv[c][1][15])));
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][0][i], a.c, -mn));
-                s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][1][i], a.c, -mn));
-            }
-            r.l = __builtin_fmaf(r.l, __builtin_amdgcn_exp2f(r.m - mn), s0 + s1);
-            r.m = mn;
-        }
-        if ((t + 1) % kRunTiles == 0 || t + 1 == t1) {  // the run's end
-            const RowMax o = {__shfl_xor(r.m, 32), __shfl_xor(r.l, 32)};
-            r = h == 0 ? merge(r, o) : merge(o, r);
-            total = t < t0 + kRunTiles ? r : merge(total, r);
-            r = {kNegBig, 0.f};
-        }
+        for (int i = 0; i < 64; i++)
+            acc += __builtin_amdgcn_exp2f(rounded_product(sv[i >> 5][(i >> 4) & 1][i & 15], a.c) - mn);
+        m = mn;
+        l = acc;
         landed();
     });
-    return total;
+    const float mo = __shfl_xor(m, 32);
+    const float lo = __shfl_xor(l, 32);
+    const float mn = max2f(m, mo);
+    const float inv = 1.0f / (l * __builtin_amdgcn_exp2f(m - mn) + lo * __builtin_amdgcn_exp2f(mo - mn));
+    const float other = __shfl_xor(inv, 32);
+    return {mn, {h == 0 ? inv : other, h == 0 ? other : inv}};
 }
 
 // log2 of a positive fp32; what is below the normal range counts as 2^-126
@@ -379,7 +378,7 @@ struct RowPlace {
 constexpr int kOutBytes = 4096;  // per wave
 template <int kOut, int kGamma, typename Landed>
 __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPlace& w, TileScores& sv, uint8_t* out,
-                                          int t, float m, float inv, RowStats<kGamma>& st, const Landed& landed) {
+                                          int t, const RowNorm& r, RowStats<kGamma>& st, const Landed& landed) {
     if constexpr (kOut == kRowsStoreP) {
 #pragma unroll
         for (int c = 0; c < 2; c++)
@@ -387,7 +386,7 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
             for (int j = 0; j < 2; j++)
 #pragma unroll
                 for (int i = 0; i < 16; i++)
-                    sv[c][j][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][j][i], a.c, -m)) * inv;
+                    sv[c][j][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][j][i], a.c, -r.m)) * r.inv[(i >> 2) & 1];
         landed();
         const int row0 = w.qt * kRowsPerWg + 32 * w.wave;
 #pragma unroll
@@ -408,9 +407,9 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
                 for (int k = 0; k < 4; k++) {
                     const int row = 4 * k + (w.lane >> 4), slot = w.lane & 15;
                     const float4 v = *reinterpret_cast<const float4*>(out + row * 256 + ((slot ^ row) * 16));
-                    const int r = row0 + 16 * pass + row, key = t * kKeyTile + 64 * c + 4 * slot;
-                    if (r < a.rows && key < a.Nkv)
-                        *reinterpret_cast<float4*>(a.p + (w.bh * a.rows + r) * (int64_t)a.ld + key) = v;
+                    const int lr = row0 + 16 * pass + row, key = t * kKeyTile + 64 * c + 4 * slot;
+                    if (lr < a.rows && key < a.Nkv)
+                        *reinterpret_cast<float4*>(a.p + (w.bh * a.rows + lr) * (int64_t)a.ld + key) = v;
                 }
                 __builtin_amdgcn_wave_barrier();
             }
@@ -421,7 +420,7 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
             float p[32], mx = 0.f;  // gamma > 0: the largest x is gamma times the largest p
 #pragma unroll
             for (int n = 0; n < 32; n++)
-                p[n] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][n >> 4][n & 15], a.c, -m)) * inv;
+                p[n] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][n >> 4][n & 15], a.c, -r.m)) * r.inv[(n >> 2) & 1];
 #pragma unroll
             for (int n = 0; n < 32; n += 2) mx = max2f(max2f(mx, p[n]), p[n + 1]);
             add_block<kRule, kGamma, 32>(st, p, a.gamma, __builtin_bit_cast(uint32_t, a.gamma * mx), a.g);
@@ -431,7 +430,7 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
 }
 
 // Rows of attention probabilities, one workgroup per 128 query rows: pass 1
-// the row maximum m and normalizer L run by run, pass 2 p.
+// the row maximum m and normalizer L, pass 2 p.
 template <int kOut, int kGamma>
 __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
@@ -439,18 +438,15 @@ __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
     const RowPlace w(a, blockIdx.x);
     bf16x8 qb[8];
     load_queries(a, w.bh, w.lr, w.h, qb);
-    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    const RowNorm r = row_norm(a, w.bh, qb, lds, w.wave, w.lane, w.col, w.h);
+
+    const KeyStage<true> ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
     const int tiles = (a.Nkv + kKeyTile - 1) / kKeyTile;
-
-    const RowMax r = row_max(a, ks, qb, lds, 0, tiles, w.col, w.h);
-    const float inv = 1.0f / r.l;
-
     RowStats<kGamma> st;
 #pragma unroll
     for (int i = 0; i < RowStats<kGamma>::kSums; i++) st.v[i] = 0.0;
-    for_tiles(qb, ks, lds, 0, tiles, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
-        emit_tile<kOut, kGamma>(a, w, sv, out + (kOut == kRowsStoreP ? w.wave * kOutBytes : 0), t, r.m, inv, st,
-                                landed);
+    for_tiles<true>(qb, ks, lds, 0, tiles, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
+        emit_tile<kOut, kGamma>(a, w, sv, out + (kOut == kRowsStoreP ? w.wave * kOutBytes : 0), t, r, st, landed);
     });
     if constexpr (kOut != kRowsStoreP) {
 #pragma unroll
@@ -459,44 +455,21 @@ __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
     }
 }
 
-// Few row tiles: one workgroup per (row tile, run).  The run's (m, l) goes to
-// the first two of the run's own entries of the row (p has room for at least
-// four there), where rows_merge_kernel leaves the row's m and 1 / L for every
-// run; a workgroup of rows_write_kernel reads that pair of its own run before
-// it overwrites it, so no other workspace is needed.
-__global__ __launch_bounds__(256, 3) void rows_partial_kernel(SoftmaxRowsArgs a) {
+// Few row tiles: m and L in one workgroup per row tile, p in one per (row tile,
+// run of kRunTiles key tiles).  Every run's (m, 1 / L) goes to the first three
+// of the run's own entries of the row (p has room for at least four there); a
+// workgroup of rows_write_kernel reads those of its own run before it overwrites
+// them, so no other workspace is needed.
+__global__ __launch_bounds__(256) void rows_norm_kernel(SoftmaxRowsArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
-    const RowPlace w(a, blockIdx.x / a.runs);
-    const int run = blockIdx.x % a.runs;
+    const RowPlace w(a, blockIdx.x);
     bf16x8 qb[8];
     load_queries(a, w.bh, w.lr, w.h, qb);
-    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
-    const int t1 = min((a.Nkv + kKeyTile - 1) / kKeyTile, (run + 1) * kRunTiles);
-    const RowMax r = row_max(a, ks, qb, lds, run * kRunTiles, t1, w.col, w.h);
-    if (w.ok && w.h == 0) *reinterpret_cast<float2*>(w.prow(a) + run * (kRunTiles * kKeyTile)) = make_float2(r.m, r.l);
-}
-
-// One wave per row: its lanes read 64 runs' pairs at once, which every lane
-// then merges in order.
-__global__ __launch_bounds__(256) void rows_merge_kernel(SoftmaxRowsArgs a, int64_t rows) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (i >= rows) return;
-    const int lane = threadIdx.x & 63;
-    float* row = a.p + i * a.ld;
-    constexpr int kStep = kRunTiles * kKeyTile;
-    RowMax r = {kNegBig, 0.f};
-    for (int run0 = 0; run0 < a.runs; run0 += 64) {
-        const float2 x = *reinterpret_cast<const float2*>(row + (int64_t)min(run0 + lane, a.runs - 1) * kStep);
-        const int n = min(64, a.runs - run0);
-        for (int e = 0; e < n; e++) {
-            const RowMax y = {__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.x), e)),
-                              __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.y), e))};
-            r = run0 + e == 0 ? y : merge(r, y);
-        }
-    }
-    const float inv = 1.0f / r.l;
-    for (int run = lane; run < a.runs; run += 64)
-        *reinterpret_cast<float2*>(row + (int64_t)run * kStep) = make_float2(r.m, inv);
+    const RowNorm r = row_norm(a, w.bh, qb, lds, w.wave, w.lane, w.col, w.h);
+    if (w.ok)
+        for (int run = w.h; run < a.runs; run += 2)
+            *reinterpret_cast<float4*>(w.prow(a) + (int64_t)run * (kRunTiles * kKeyTile)) =
+                make_float4(r.m, r.inv[0], r.inv[1], 0.f);
 }
 
 __global__ __launch_bounds__(256, 3) void rows_write_kernel(SoftmaxRowsArgs a) {
@@ -506,14 +479,17 @@ __global__ __launch_bounds__(256, 3) void rows_write_kernel(SoftmaxRowsArgs a) {
     const int run = blockIdx.x % a.runs;
     bf16x8 qb[8];
     load_queries(a, w.bh, w.lr, w.h, qb);
-    const KeyStage ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
-    float2 mi = make_float2(0.f, 0.f);
-    if (w.ok) mi = *reinterpret_cast<const float2*>(w.prow(a) + run * (kRunTiles * kKeyTile));
+    const KeyStage<true> ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    RowNorm r = {0.f, {0.f, 0.f}};
+    if (w.ok) {
+        const float4 v = *reinterpret_cast<const float4*>(w.prow(a) + (int64_t)run * (kRunTiles * kKeyTile));
+        r = {v.x, {v.y, v.z}};
+    }
     RowStats<kGammaOne> st;
     const int t1 = min((a.Nkv + kKeyTile - 1) / kKeyTile, (run + 1) * kRunTiles);
-    // (the wait for the first tile is also one for the pair)
-    for_tiles(qb, ks, lds, run * kRunTiles, t1, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
-        emit_tile<kRowsStoreP, kGammaOne>(a, w, sv, out + w.wave * kOutBytes, t, mi.x, mi.y, st, landed);
+    // (the wait for the first tile is also one for the row's values)
+    for_tiles<true>(qb, ks, lds, run * kRunTiles, t1, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
+        emit_tile<kRowsStoreP, kGammaOne>(a, w, sv, out + w.wave * kOutBytes, t, r, st, landed);
     });
 }
 
@@ -618,18 +594,14 @@ hipError_t launch_attn_rows(const SoftmaxRowsArgs& args, int64_t BH, int out, hi
         return hipGetLastError();
     }
     // 768 workgroups (three per CU) fill the chip: with fewer row tiles each
-    // run of keys gets a workgroup of its own
+    // run of keys gets a workgroup of its own for p
     if (a.runs < 2 || tiles >= 768) {
         attn_rows_kernel<kRowsStoreP, kGammaOne><<<dim3((unsigned)tiles), 256, 0, stream>>>(a);
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)(tiles * a.runs));
-    rows_partial_kernel<<<grid, 256, 0, stream>>>(a);
+    rows_norm_kernel<<<dim3((unsigned)tiles), 256, 0, stream>>>(a);
     if (hipError_t e = hipGetLastError()) return e;
-    const int64_t rows = BH * a.rows;
-    rows_merge_kernel<<<dim3((unsigned)((rows + 3) / 4)), 256, 0, stream>>>(a, rows);
-    if (hipError_t e = hipGetLastError()) return e;
-    rows_write_kernel<<<grid, 256, 0, stream>>>(a);
+    rows_write_kernel<<<dim3((unsigned)(tiles * a.runs)), 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 
