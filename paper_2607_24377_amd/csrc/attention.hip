@@ -1076,7 +1076,7 @@ __device__ __forceinline__ void resident_tile(const uint8_t* st, const LaneOff& 
 // with no per-tile loads or barriers; each query tile is the same computation
 // as in the streaming kernel, with kTiles = 1 to 4 key tiles in a row (as a
 // loop over a run-time count the 128 registers of scores and O~ met at every
-// branch and spilled).  512 keys: vector issue busy 77 % and 0.45 ms at 40 heads
+// branch and spilled).  512 keys: vector issue busy 81 % and 0.45 ms at 40 heads
 // x 75600 queries, of which reading Q and writing O takes 0.30; scoring the next
 // tile under the softmax gained 1 to 6 % (5 heads x 20000 queries 29.0 -> 27.6
 // us) over issuing each tile's products as one group.
