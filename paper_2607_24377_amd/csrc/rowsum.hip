@@ -41,7 +41,7 @@
 // vector instructions per entry over the two passes: 40 heads x 4096^2 entries
 // in 0.75 ms; with every class summed per entry in fp64 behind compares and
 // selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries the chain
-// of L in 40 workgroups, one wave per SIMD (@NORM ms), then HBM (P written, 0.25
+// of L in 40 workgroups, one wave per SIMD (0.41 ms), then HBM (P written, 0.25
 // ms; both passes in one workgroup per row tile 2.9 ms), and their diagnostic
 // again vector issue (0.20 ms = 3.3 TB/s of P; before 0.24 ms).
 #include <cmath>
@@ -116,17 +116,13 @@ __device__ __forceinline__ v16f scores_t(const bf16x8* qb, const uint8_t* lds, i
     return acc;
 }
 
-// The scores of the staged tile, -inf past the end of the sequence: sv[c][j][i]
-// is key 64 c + 32 h + 16 j + i with kBlocks, otherwise 64 c + 32 j + 8 (i >> 2)
-// + 4 h + (i & 3).
+// The scores of a tile: sv[c][j][i] is key 64 c + 32 h + 16 j + i with kBlocks,
+// otherwise 64 c + 32 j + 8 (i >> 2) + 4 h + (i & 3).
 typedef v16f TileScores[2][2];
+
+// -inf past the end of the sequence.
 template <bool kBlocks>
-__device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds, int t, int Nkv, int col, int h,
-                                            TileScores& sv) {
-#pragma unroll
-    for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) sv[c][j] = scores_t(qb, lds, 2 * c + j, col, h);
+__device__ __forceinline__ void mask_tail(int t, int Nkv, int h, TileScores& sv) {
     if ((t + 1) * kKeyTile > Nkv) {
         const int valid = Nkv - t * kKeyTile - (kBlocks ? 32 : 4) * h;
 #pragma unroll
@@ -135,8 +131,19 @@ __device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds
             for (int j = 0; j < 2; j++)
 #pragma unroll
                 for (int i = 0; i < 16; i++)
-                    if (64 * c + (kBlocks ? 16 * j + i : 32 * j + 8 * (i >> 2) + (i & 3)) >= valid) sv[c][j][i] = -INFINITY;
+                    if (64 * c + (kBlocks ? 16 * j + i : 32 * j + 8 * (i >> 2) + (i & 3)) >= valid)
+                        sv[c][j][i] = -INFINITY;
     }
+}
+
+template <bool kBlocks>
+__device__ __forceinline__ void tile_scores(const bf16x8* qb, const uint8_t* lds, int t, int Nkv, int col, int h,
+                                            TileScores& sv) {
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) sv[c][j] = scores_t(qb, lds, 2 * c + j, col, h);
+    mask_tail<kBlocks>(t, Nkv, h, sv);
 }
 
 // Calls work(t, scores, landed) for the tiles t0 .. t1 - 1.  The next tile is
@@ -182,32 +189,46 @@ __device__ __forceinline__ float rounded_product(float s, float c) {
     return s * c;
 }
 
-__device__ __forceinline__ RowNorm row_norm(const SoftmaxRowsArgs& a, int64_t bh, const bf16x8* qb, uint8_t* lds,
-                                            int wave, int lane, int col, int h) {
-    const KeyStage<false> ks(a.k, bh, a.Nkv, wave, lane);
+// A lane's running maximum and sum.  A tile updates the maximum (grow) and then
+// adds its 64 entries in key order (add).
+struct LaneNorm {
     float m = kNegBig, l = 0.f;
-    for_tiles<false>(qb, ks, lds, 0, (a.Nkv + kKeyTile - 1) / kKeyTile, col, h, [&](int, TileScores& sv, auto landed) {
+
+    __device__ __forceinline__ void grow(const TileScores& sv, float c) {
         float tm = sv[0][0][0];
 #pragma unroll
         for (int i = 1; i < 63; i += 2)
             tm = max2f(max2f(tm, sv[i >> 5][(i >> 4) & 1][i & 15]), sv[(i + 1) >> 5][((i + 1) >> 4) & 1][(i + 1) & 15]);
         tm = max2f(tm, sv[1][1][15]);
         // (a lane whose keys are all past the end keeps m: c tm = -inf)
-        const float mn = max2f(m, rounded_product(tm, a.c));
-        float acc = l * __builtin_amdgcn_exp2f(m - mn);
-#pragma unroll
-        for (int i = 0; i < 64; i++)
-            acc += __builtin_amdgcn_exp2f(rounded_product(sv[i >> 5][(i >> 4) & 1][i & 15], a.c) - mn);
+        const float mn = max2f(m, rounded_product(tm, c));
+        l = l * __builtin_amdgcn_exp2f(m - mn);
         m = mn;
-        l = acc;
+    }
+    __device__ __forceinline__ void add(float s, float c) {
+        l += __builtin_amdgcn_exp2f(rounded_product(s, c) - m);
+    }
+    __device__ __forceinline__ RowNorm row(int h) const {
+        const float mo = __shfl_xor(m, 32);
+        const float lo = __shfl_xor(l, 32);
+        const float mn = max2f(m, mo);
+        const float inv = 1.0f / (l * __builtin_amdgcn_exp2f(m - mn) + lo * __builtin_amdgcn_exp2f(mo - mn));
+        const float other = __shfl_xor(inv, 32);
+        return {mn, {h == 0 ? inv : other, h == 0 ? other : inv}};
+    }
+};
+
+__device__ __forceinline__ RowNorm row_norm(const SoftmaxRowsArgs& a, int64_t bh, const bf16x8* qb, uint8_t* lds,
+                                            int wave, int lane, int col, int h) {
+    const KeyStage<false> ks(a.k, bh, a.Nkv, wave, lane);
+    LaneNorm n;
+    for_tiles<false>(qb, ks, lds, 0, (a.Nkv + kKeyTile - 1) / kKeyTile, col, h, [&](int, TileScores& sv, auto landed) {
+        n.grow(sv, a.c);
+#pragma unroll
+        for (int i = 0; i < 64; i++) n.add(sv[i >> 5][(i >> 4) & 1][i & 15], a.c);
         landed();
     });
-    const float mo = __shfl_xor(m, 32);
-    const float lo = __shfl_xor(l, 32);
-    const float mn = max2f(m, mo);
-    const float inv = 1.0f / (l * __builtin_amdgcn_exp2f(m - mn) + lo * __builtin_amdgcn_exp2f(mo - mn));
-    const float other = __shfl_xor(inv, 32);
-    return {mn, {h == 0 ? inv : other, h == 0 ? other : inv}};
+    return n.row(h);
 }
 
 // log2 of a positive fp32; what is below the normal range counts as 2^-126
@@ -460,12 +481,62 @@ __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
 // of the run's own entries of the row (p has room for at least four there); a
 // workgroup of rows_write_kernel reads those of its own run before it overwrites
 // them, so no other workspace is needed.
+//
+// One wave per SIMD: rows_norm_kernel scores tile t + 1 (a product after every
+// two entries) while the chain of tile t is added, with two tiles in LDS and
+// the next in flight.  40 heads x 128 rows x 32760 keys 413 us; scoring each tile
+// before its chain 475 us.
 __global__ __launch_bounds__(256) void rows_norm_kernel(SoftmaxRowsArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kKeyTile * 256];
+    // (two arrays: reads of one do not wait for copies into the other)
+    __shared__ __attribute__((aligned(16))) uint8_t lds0[kKeyTile * 256];
+    __shared__ __attribute__((aligned(16))) uint8_t lds1[kKeyTile * 256];
     const RowPlace w(a, blockIdx.x);
     bf16x8 qb[8];
     load_queries(a, w.bh, w.lr, w.h, qb);
-    const RowNorm r = row_norm(a, w.bh, qb, lds, w.wave, w.lane, w.col, w.h);
+    const KeyStage<false> ks(a.k, w.bh, a.Nkv, w.wave, w.lane);
+    const int tiles = (a.Nkv + kKeyTile - 1) / kKeyTile;
+    LaneNorm n;
+
+    // tile t, its scores in sv and its keys in cur; leaves tile t + 1's scores, from nxt
+    auto step = [&](int t, uint8_t* cur, const uint8_t* nxt, TileScores& sv, TileScores& next) {
+        __syncthreads();  // tile t was read everywhere, tile t + 1 landed everywhere
+        if (t + 2 < tiles) ks.load(cur, t + 2);
+        n.grow(sv, a.c);
+#pragma unroll
+        for (int p = 0; p < 4; p++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) next[p >> 1][p & 1][i] = 0.f;
+        auto operand = [&](int k) {  // key rows 32 (k & 3) + col, channels of step k >> 2
+            return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+                nxt + (32 * (k & 3) + w.col) * 256 + (((2 * (k >> 2) + w.h) ^ (w.col & 15)) * 16)));
+        };
+        bf16x8 ka[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) ka[k] = operand(k);
+#pragma unroll
+        for (int k = 0; k < 32; k++) {
+            v16f& acc = next[(k >> 1) & 1][k & 1];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[k & 3], qb[k >> 2], acc, 0, 0, 0);
+            if (k + 4 < 32) ka[k & 3] = operand(k + 4);
+#pragma unroll
+            for (int e = 2 * k; e < 2 * k + 2; e++) n.add(sv[e >> 5][(e >> 4) & 1][e & 15], a.c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mask_tail<false>(t + 1, a.Nkv, w.h, next);
+        __builtin_amdgcn_s_waitcnt(0);
+    };
+    ks.load(lds0, 0);
+    if (tiles > 1) ks.load(lds1, 1);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    TileScores s0, s1;
+    tile_scores<false>(qb, lds0, 0, a.Nkv, w.col, w.h, s0);
+    // (after the last tile the scores of whatever is staged are formed and dropped)
+    for (int t = 0; t < tiles; t += 2) {
+        step(t, lds0, lds1, s0, s1);
+        if (t + 1 < tiles) step(t + 1, lds1, lds0, s1, s0);
+    }
+    const RowNorm r = n.row(w.h);
     if (w.ok)
         for (int run = w.h; run < a.runs; run += 2)
             *reinterpret_cast<float4*>(w.prow(a) + (int64_t)run * (kRunTiles * kKeyTile)) =
