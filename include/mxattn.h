@@ -291,10 +291,13 @@ const char* mxattn_last_error(void);
  * created on first use; the device's default pool is left as it is).  The
  * pool keeps freed workspace for the next call rather than returning it to
  * the driver; one block of at most 64 MiB per device stays allocated for the
- * calls on the null stream that fit it.  mxattn_release_workspace returns all of the current device's
- * cached workspace that no call still uses; call it after the streams that
- * ran the library's calls have completed, e.g. before a phase of a pipeline
- * that needs the memory.  Returns MXATTN_OK or MXATTN_ERR_HIP. */
+ * calls on the null stream that fit it.  mxattn_release_workspace returns all
+ * of the current device's cached workspace that no call still uses, and waits
+ * for none: call it after the streams that ran the library's calls have
+ * completed, e.g. before a phase of a pipeline that needs the memory.  The
+ * kept block stays while the null stream has work, or while a stream that
+ * synchronizes with it is being captured.  Returns MXATTN_OK or
+ * MXATTN_ERR_HIP. */
 int mxattn_release_workspace(void);
 
 /* ABI version (major * 100 + minor). */

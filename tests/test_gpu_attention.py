@@ -6,6 +6,8 @@ remaining differences are v_exp_f32's faithful (not always correctly rounded)
 exponential, which can move an element of P~ across an E2M1 decision
 threshold, and fp32 vs fp64 accumulation.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -246,6 +248,55 @@ def test_workspace_across_streams_and_threads(mx):
     work(null, [0, 2])
     torch.cuda.synchronize()
     assert not bad, bad
+
+
+def test_release_does_not_wait_for_the_null_stream(mx):
+    """A release while calls are under way returns at once; the block that they
+    use is given back by a release after they have completed."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, 8, 4000, 128), generator=g, device="cuda").bfloat16() for _ in range(3))
+    null = torch.cuda.default_stream()
+    with torch.cuda.stream(null):
+        want = mx.forward(q, k, v, "uos_pnq")
+        out = torch.empty_like(want)
+        torch.cuda.synchronize()
+        for _ in range(200):  # about 10 ms of GPU work, enqueued in 2
+            mx.forward(q, k, v, "uos_pnq", out=out)
+        done = null.record_event()
+        mx.release_workspace()
+        assert not done.query()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+        free = torch.cuda.mem_get_info()[0]
+        mx.release_workspace()
+        assert torch.cuda.mem_get_info()[0] > free
+        again = mx.forward(q, k, v, "uos_pnq")
+    assert torch.equal(again.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("flags", [1, 0])  # hipStreamNonBlocking, hipStreamDefault
+def test_release_beside_a_capture(mx, flags):
+    """A release while another stream is captured leaves the capture alone, also
+    where that stream synchronizes with the null stream (flags 0)."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    x = torch.zeros((1, 1, 64, 128), dtype=torch.bfloat16, device="cuda")
+    with torch.cuda.stream(torch.cuda.default_stream()):
+        mx.forward(x, x, x, "uos_pnq")
+    torch.cuda.synchronize()
+    stream, graph, status = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_int(-1)
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(stream), flags) == 0
+    try:
+        assert hip.hipStreamBeginCapture(stream, 0) == 0
+        mx.release_workspace()
+        assert hip.hipStreamIsCapturing(stream, ctypes.byref(status)) == 0 and status.value == 1
+        assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+        assert hip.hipGraphDestroy(graph) == 0
+    finally:
+        hip.hipStreamDestroy(stream)
+    mx.release_workspace()
+    with torch.cuda.stream(torch.cuda.default_stream()):
+        out = mx.forward(x, x, x, "uos_pnq")
+    assert torch.count_nonzero(out) == 0
 
 
 def _edge_q_rows(q):
