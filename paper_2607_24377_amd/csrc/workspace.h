@@ -131,9 +131,14 @@ class Workspace {
 
   private:
     // A block of at least `bytes` (the next power of two from 1 MiB on) in place
-    // of k's; k is empty if it cannot be had.
+    // of k's; k is empty if it cannot be had, and as it was if its own block
+    // cannot be freed.  Either way the call's workspace comes from the pool, and
+    // no error is left for the launches that follow.
     static void grow(KeptBlock& k, size_t bytes) {
-        if (k.p) (void)hipFreeAsync(k.p, nullptr);
+        if (k.p && hipFreeAsync(k.p, nullptr) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
         k.p = nullptr;
         k.bytes = 0;
         size_t n = (size_t)1 << 20;
@@ -152,30 +157,40 @@ class Workspace {
 };
 
 // Gives k's block back to the pool if no call can still use it, without waiting
-// for one: the block stays where the null stream has work, and where a stream
-// that synchronizes with the null stream is being captured (an operation on the
-// null stream is not allowed then: the free and the wait below ended the
-// process).  The query of the capture is allowed always and disturbs none.
-void release_kept(KeptBlock& k) {
-    if (!k.p) return;
+// for one; MXATTN_ERR_HIP if that fails.  The block stays where the null stream
+// has work, and where a stream that synchronizes with the null stream is being
+// captured (an operation on the null stream is not allowed then: the free and
+// the wait below ended the process).  The query of the capture is allowed
+// always and disturbs none.
+int release_kept(KeptBlock& k) {
+    if (!k.p) return MXATTN_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(nullptr, &capture) != hipSuccess) {
         (void)hipGetLastError();
-        return;
+        return MXATTN_OK;
     }
     // (queries and waits are allowed then also while another stream is captured)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (hipStreamQuery(nullptr) == hipSuccess) {
-        (void)hipFreeAsync(k.p, nullptr);
-        k.p = nullptr;
-        k.bytes = 0;
-        // the free is through before the trim; the stream holds nothing else
-        if (hipStreamSynchronize(nullptr) != hipSuccess) (void)hipGetLastError();
-    } else {
-        (void)hipGetLastError();  // hipErrorNotReady
+    const char* what = "hipStreamQuery";
+    hipError_t e = hipStreamQuery(nullptr);
+    if (e == hipSuccess) {
+        what = "hipFreeAsync";
+        e = hipFreeAsync(k.p, nullptr);
+        if (e == hipSuccess) {
+            k.p = nullptr;
+            k.bytes = 0;
+            // the free is through before the trim; the stream holds nothing else
+            what = "hipStreamSynchronize";
+            e = hipStreamSynchronize(nullptr);
+        }
     }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) return MXATTN_OK;
+    (void)hipGetLastError();
+    if (e == hipErrorNotReady) return MXATTN_OK;
+    set_error(what, e);
+    return MXATTN_ERR_HIP;
 }
 
 int release_workspace() {
@@ -186,18 +201,19 @@ int release_workspace() {
         return MXATTN_ERR_HIP;
     }
     if (dev < 0 || dev >= kMaxDevices) return MXATTN_OK;
+    int st = MXATTN_OK;
     {
         std::lock_guard<std::mutex> lock(g_kept[dev].m);
-        release_kept(g_kept[dev]);
+        st = release_kept(g_kept[dev]);
     }
     hipMemPool_t pool = g_pools[dev].pool.load();
-    if (!pool) return MXATTN_OK;  // no workspace was ever taken on this device
+    if (!pool) return st;  // no workspace was ever taken on this device
     e = hipMemPoolTrimTo(pool, 0);
     if (e != hipSuccess) {
         set_error("hipMemPoolTrimTo", e);
         return MXATTN_ERR_HIP;
     }
-    return MXATTN_OK;
+    return st;
 }
 
 }  // namespace

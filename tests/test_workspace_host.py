@@ -54,3 +54,28 @@ def test_release_beside_a_capture_leaves_the_null_stream_alone(run):
     assert calls == ["capturing", "trim"]
     assert rel["status"] == 0 and rel["kept"] == 4 * MIB and rel["last"] == 0
     assert last["live"] == 0
+
+
+def test_refused_free_keeps_the_block(run):
+    """A free that is refused loses no block, is reported by the release, and
+    leaves no error behind for the launches of the call that wanted more."""
+    _, (_, grow, c0), (_, rel, c1), (_, again, c2), (_, last, _) = run("grow", "free=1")
+    assert c0 == ["free", "alloc", "free"]  # refused; pool memory of the call's own, whose free is refused too
+    assert grow["kept"] == 4 * MIB and grow["live"] == 2
+    assert rel["status"] == 8 and rel["detail"] == 1 and rel["kept"] == 4 * MIB and rel["live"] == 2
+    assert c1[-1] == "trim" and c1[-2] == "global" and "wait" not in c1
+    assert c2 == [] and last["status"] == 0 and last["live"] == 1  # the pool memory that the call could not free
+
+
+def test_release_reports_a_failed_wait(run):
+    _, (_, rel, _), _, (_, last, _) = run("wait=1")
+    assert rel["status"] == 8 and rel["detail"] == 1 and rel["kept"] == 0 and rel["last"] == 0
+    assert last["status"] == 0 and last["live"] == 0
+
+
+def test_block_that_cannot_grow(run):
+    """No memory for a larger block: the old one is given back, the call reports
+    that it has no workspace either."""
+    _, (_, grow, c), _, (_, again, _), (_, last, _) = run("grow", "alloc=2")
+    assert c == ["free", "alloc", "alloc"] and grow["status"] == 7 and grow["kept"] == 0 and grow["live"] == 0
+    assert again["kept"] == 4 * MIB and last["live"] == 0
