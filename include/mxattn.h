@@ -178,6 +178,8 @@ int mxattn_qmax_sse(const void* x, int block_axis, const double* qs, int nq, dou
  * mxattn_rowsum_diag quantizes given rows:
  *   p       device fp32 [rows, ld], entries >= 0 (first N of each row used),
  *           ld >= N, ld % 4 == 0, 16-byte aligned
+ *           (an infinite entry makes [1] and [3] infinite, a NaN entry makes [1]
+ *           and [6] NaN, for every gamma)
  *   stats   device fp64 [rows, 8]
  * mxattn_attention_rowsum_diag computes the same statistics for every query
  * row of q against k without materializing P: the probabilities are formed

@@ -263,15 +263,17 @@ __device__ __forceinline__ uint32_t cvt_u32_neg(float x) {
 // entries of a block add up exactly in 32-bit integers (at most 32 * 2 * 2^25),
 // one fp64 product and sum per block each; only zeroed entries and the entropy
 // take an fp64 sum per entry.  Otherwise every entry's terms are formed and
-// added in fp64.
+// added in fp64, as they are where an entry is not a finite number >= 0
+// (add_unusual).
 enum Gamma { kGammaOne = 0, kGammaPow2 = 1, kGammaAny = 2 };
 template <int kGamma>
 struct RowStats {
     static constexpr bool kPow2 = kGamma != kGammaAny;
     // kPow2: sum Q, up, down, saturated (the last two positive), zeroed p, p log2 p;
     // otherwise the eight statistics, the last as sum p log2 p
-    static constexpr int kSums = kPow2 ? 6 : 8;
+    static constexpr int kSums = kPow2 ? 6 : 8, kEntropy = kSums - 1;
     double v[kSums];
+    bool nan = false;  // kPow2: a p is NaN (the mass and the exact entries' sum are, then)
 };
 
 // Adds this lane's kN entries of a block whose largest x has the bits mb.
@@ -349,19 +351,58 @@ __device__ __forceinline__ void add_block(RowStats<kGamma>& st, const float (&p)
     }
 }
 
+// The same for one entry of any block, also of one with an entry that is infinite
+// (x may be although p is not), NaN or negative: its terms from their definition.
+template <int kRule, int kGamma>
+__device__ __forceinline__ void add_unusual(RowStats<kGamma>& st, float p, float gamma, uint32_t mb, double g) {
+    const int ex = block_exponent_f32<kRule>(mb);
+    const float sf = e8m0_as_f32((uint32_t)(ex + 127));
+    const float inv = __builtin_bit_cast(float, (uint32_t)(127 - ex) << 23);
+    const double sig = __builtin_bit_cast(double, (uint64_t)(ex + 1023) << 52);
+    const uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, gamma * p, 0.f, sf, 0);
+    const float r = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, 1.0f, 0)[0];
+    const float xs = gamma * p * inv;
+    const double qv = (double)r * sig * g;
+    const double cj = qv - (double)p;
+    const bool zer = p > 0.f && r == 0.f;
+    const bool sat = !zer && xs > 6.0f;
+    const bool dn = !zer && !sat && r < xs;
+    const bool up = !zer && !sat && r > xs;
+    const bool eq = !zer && !sat && !dn && !up;
+    const double plog = p > 0.f ? (double)(p * log2_full(p)) : 0.0;
+    st.v[0] += qv;
+    if constexpr (kGamma != kGammaAny) {
+        st.v[1] += up ? cj : 0.0;
+        st.v[2] -= dn ? cj : 0.0;
+        st.v[3] -= sat ? cj : 0.0;
+        st.v[4] -= zer ? cj : 0.0;
+        st.v[5] += plog;
+        st.nan |= p != p;
+    } else {
+        st.v[1] += (double)p;
+        st.v[2] += zer ? cj : 0.0;
+        st.v[3] += sat ? cj : 0.0;
+        st.v[4] += dn ? cj : 0.0;
+        st.v[5] += up ? cj : 0.0;
+        st.v[6] += eq ? cj : 0.0;
+        st.v[7] += plog;
+    }
+}
+
 // The eight statistics of a row from its sums over all lanes.
 template <int kGamma>
 __device__ __forceinline__ void write_stats(double* dst, const RowStats<kGamma>& st) {
     constexpr double kMinusLn2 = -0.6931471805599453;  // -sum p ln p = -ln 2 sum p log2 p
     if constexpr (kGamma != kGammaAny) {
         const double R = st.v[0], up = st.v[1], down = st.v[2], sat = st.v[3], z = st.v[4];
+        const double eq = st.nan ? __builtin_nan("") : 0.0;
         dst[0] = R;
-        dst[1] = R + z + ((down + sat) - up);  // the mass: what was quantized less what it gained
-        dst[2] = -z;
-        dst[3] = -sat;
-        dst[4] = -down;
+        dst[1] = R + z + ((down + sat) - up) - eq;  // the mass: what was quantized less what it gained
+        dst[2] = 0.0 - z;
+        dst[3] = 0.0 - sat;
+        dst[4] = 0.0 - down;
         dst[5] = up;
-        dst[6] = 0.0;
+        dst[6] = eq;
         dst[7] = kMinusLn2 * st.v[5];
     } else {
 #pragma unroll
@@ -444,10 +485,20 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
                 p[n] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[c][n >> 4][n & 15], a.c, -r.m)) * r.inv[(n >> 2) & 1];
 #pragma unroll
             for (int n = 0; n < 32; n += 2) mx = max2f(max2f(mx, p[n]), p[n + 1]);
-            add_block<kRule, kGamma, 32>(st, p, a.gamma, __builtin_bit_cast(uint32_t, a.gamma * mx), a.g);
+            add_block<kRule, kGamma, 32>(st, p, a.gamma, __builtin_bit_cast(uint32_t, a.gamma * __builtin_fabsf(mx)),
+                                         a.g);
         }
         landed();
     }
+}
+
+// The entries between the last key and the next multiple of 4 are 0, since the
+// score of a key past the end is -inf; but NaN in a row whose maximum or normalizer
+// is not finite, where 0 is stored over them.
+__device__ __forceinline__ void clear_past_end(const SoftmaxRowsArgs& a, const RowPlace& w, const RowNorm& r) {
+    if ((a.Nkv & 3) == 0 || r.inv[0] < INFINITY || !w.ok || w.h != 0) return;
+    __builtin_amdgcn_s_waitcnt(0);  // the wave's stores to the same entries
+    for (int64_t j = a.Nkv; (j & 3) != 0; j++) w.prow(a)[j] = 0.f;
 }
 
 // Rows of attention probabilities, one workgroup per 128 query rows: pass 1
@@ -469,9 +520,18 @@ __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
     for_tiles<true>(qb, ks, lds, 0, tiles, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
         emit_tile<kOut, kGamma>(a, w, sv, out + (kOut == kRowsStoreP ? w.wave * kOutBytes : 0), t, r, st, landed);
     });
-    if constexpr (kOut != kRowsStoreP) {
+    if constexpr (kOut == kRowsStoreP) {
+        clear_past_end(a, w, r);
+    } else {
 #pragma unroll
         for (int i = 0; i < RowStats<kGamma>::kSums; i++) st.v[i] += __shfl_xor(st.v[i], 32);
+        // p is at most 1, or NaN in the whole row: a NaN is quantized to +-6 at the
+        // scale 2^126, is in no class but "exact" and has no entropy
+        if (!(r.inv[0] < INFINITY)) {
+            st.v[0] = __builtin_copysign((double)a.Nkv * (6.0 * 0x1p126 * a.g), st.v[0]);
+            st.v[RowStats<kGamma>::kEntropy] = 0.0;
+            st.nan = true;
+        }
         if (w.ok && w.h == 0) write_stats(a.stats + (w.bh * a.Nq + a.row0 + w.lr) * 8, st);
     }
 }
@@ -562,6 +622,7 @@ __global__ __launch_bounds__(256, 3) void rows_write_kernel(SoftmaxRowsArgs a) {
     for_tiles<true>(qb, ks, lds, run * kRunTiles, t1, w.col, w.h, [&](int t, TileScores& sv, auto landed) {
         emit_tile<kRowsStoreP, kGammaOne>(a, w, sv, out + w.wave * kOutBytes, t, r, st, landed);
     });
+    if (run == a.runs - 1) clear_past_end(a, w, r);
 }
 
 // One workgroup per row; 4 lanes per 32-entry block, 8 entries per lane.
@@ -569,6 +630,7 @@ template <int kRule, int kGamma>
 __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
     constexpr int kSums = RowStats<kGamma>::kSums;
     __shared__ double red[4][kSums];
+    __shared__ int flags[4];
     const int64_t r = blockIdx.x;
     const float* prow = a.p + r * a.ld;
     RowStats<kGamma> st;
@@ -576,14 +638,18 @@ __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
     for (int i = 0; i < kSums; i++) st.v[i] = 0.0;
     const float gamma = kGamma == kGammaOne ? 1.0f : a.gamma;
 
-    auto block = [&](const float (&p)[8]) {
-        float mx = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2)
-            mx = max2f(max2f(mx, __builtin_fabsf(gamma * p[e])), __builtin_fabsf(gamma * p[e + 1]));
-        uint32_t mb = __builtin_bit_cast(uint32_t, mx);
+    auto quad_max = [](uint32_t mb) {
         mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0xB1, 0xF, 0xF, false));  // lane ^ 1
-        mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0x4E, 0xF, 0xF, false));  // lane ^ 2
+        return max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0x4E, 0xF, 0xF, false));  // lane ^ 2
+    };
+    uint32_t worst = 0;
+    auto block = [&](const float (&p)[8]) {
+        // as unsigned numbers, the bits of finite x >= 0 lie below those of all others
+        uint32_t mb = 0;
+#pragma unroll
+        for (int e = 0; e < 8; e++) mb = max(mb, __builtin_bit_cast(uint32_t, gamma * p[e]));
+        mb = quad_max(mb);
+        worst = max(worst, mb);
         add_block<kRule, kGamma, 8>(st, p, a.gamma, mb, a.g);
     };
     // entries 8 t .. 8 t + 7 of each whole step of 2048, the next step's
@@ -616,15 +682,39 @@ __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
         }
         block(p);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-        for (int i = 0; i < kSums; i++) st.v[i] += __shfl_xor(st.v[i], off);
     const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
+    auto reduce = [&](bool flag) {
 #pragma unroll
-        for (int i = 0; i < kSums; i++) red[wave][i] = st.v[i];
-    __syncthreads();
+        for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < kSums; i++) st.v[i] += __shfl_xor(st.v[i], off);
+        flag = __any(flag);
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+            for (int i = 0; i < kSums; i++) red[wave][i] = st.v[i];
+            flags[wave] = flag;
+        }
+        __syncthreads();
+        return (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+    };
+    // a row with an entry that is not a finite x >= 0 is formed again from the
+    // definitions, 8 entries of a lane one at a time
+    if (reduce(worst >= 0x7F800000u)) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSums; i++) st.v[i] = 0.0;
+        for (int64_t base = 0; base < a.N; base += 2048) {
+            const int64_t j = base + 8 * threadIdx.x;
+            uint32_t mb = 0;
+#pragma unroll 1
+            for (int64_t i = j; i < j + 8 && i < a.N; i++)
+                mb = max(mb, __builtin_bit_cast(uint32_t, gamma * prow[i]) & 0x7FFFFFFFu);
+            mb = quad_max(mb);
+#pragma unroll 1
+            for (int64_t i = j; i < j + 8 && i < a.N; i++) add_unusual<kRule, kGamma>(st, prow[i], a.gamma, mb, a.g);
+        }
+        st.nan = reduce(st.nan);
+    }
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 0; i < kSums; i++) st.v[i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);

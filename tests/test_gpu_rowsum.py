@@ -216,6 +216,76 @@ def test_rowsum_diag_edges(mx, mode, gamma):
         _diag_check(mx, P, N, mode, gamma, f"{mode} gamma={gamma} N={N}")
 
 
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("gamma", [1.0, 8.0, 1.37])
+@pytest.mark.parametrize("N", [100, 4100])
+def test_rowsum_diag_unusual_entries(mx, mode, gamma, N):
+    """Infinite, NaN, overflowing and negative entries in the first, a middle
+    and the ragged last block.  The scale of a block of an infinite entry is
+    2^126, at which its other entries are zeroed: an infinite row mass and
+    saturation, or a NaN mass and "exact", and the other statistics those of the
+    finite entries.  Negative entries are quantized as numbers, signs kept."""
+    ld = (N + 3) // 4 * 4
+    base = _random_rows(N, 1, N, 1.0)[0]
+    cols = (3, N // 2, N - 1)
+    for j in cols:
+        blk = slice(j // 32 * 32, min(N, j // 32 * 32 + 32))
+        rest = base.copy()
+        rest[blk] = 0.0
+        others = np.delete(base[blk], j % 32).astype(np.float64).sum()
+        finite = base.copy()
+        finite[j] = 0.0
+        P = np.zeros((5, ld), np.float32)
+        P[:, :N] = base
+        P[0, j], P[1, j], P[2, j], P[3, j], P[4, j] = np.inf, np.nan, 1e38, -0.01, -1e-6
+        got = mx.rowsum_diag(torch.from_numpy(P).cuda(), N, mode, gamma).cpu().numpy()
+        want = oracle.rowsum_diag(rest[None], N, MODES[mode], gamma)[0]
+        entropy = oracle.rowsum_diag(finite[None], N, MODES[mode], gamma)[0, 7]
+        top = 6.0 * 2.0 ** 126 / float(np.float32(gamma))  # gamma is fp32
+        label = f"{mode} gamma={gamma} N={N} column {j}"
+        for r in (0, 1):
+            assert abs(got[r, 2] - (want[2] - others)) <= 1e-11, label
+            assert np.all(np.abs(got[r, 4:6] - want[4:6]) <= 1e-11), label
+            assert abs(got[r, 0] / top - 1.0) <= 1e-12, label
+        assert np.isposinf(got[0, 1]) and np.isneginf(got[0, 3]) and got[0, 6] == 0.0, (label, got[0])
+        assert np.isneginf(got[0, 7]), label
+        assert np.isnan(got[1, 1]) and np.isnan(got[1, 6]) and abs(got[1, 3] - want[3]) <= 1e-11, (label, got[1])
+        assert abs(got[1, 7] - entropy) <= 1e-6 * entropy, label
+        # the oracle takes finite rows of either sign; an x that overflows is 1e38 of mass
+        neg = oracle.rowsum_diag(P[3:], N, MODES[mode], gamma)
+        assert np.all(np.abs(got[3:, :7] - neg[:, :7]) <= 1e-11), (label, got[3:], neg)
+        assert np.all(np.abs(got[3:, 7] - neg[:, 7]) <= 1e-6 * neg[:, 7]), label
+        assert abs(got[2, 1] / float(np.float32(1e38)) - 1.0) <= 1e-12, (label, got[2])
+        change = got[2, 2:7].sum() / (got[2, 0] - got[2, 1])
+        assert abs(change - 1.0) <= 1e-9, (label, got[2])
+
+
+def test_rows_without_a_finite_normalizer(mx):
+    """Scores that overflow make a row of NaN: p past the end is 0 all the same,
+    the statistics are those of such a row, and the other rows are not touched."""
+    w = inputs.custom(1, 2, 1100, kind="iid", index=35)
+    q, k, _ = inputs.generate(w)
+    for nkv in (301, 1099):
+        qt = mx.bf16_from_bits(np.ascontiguousarray(q[:, :, :200]))
+        kt = mx.bf16_from_bits(np.ascontiguousarray(k[:, :, :nkv]))
+        good = mx.softmax_rows(qt, kt)
+        qt[:, :, 77] = 1e30  # times 1e-2 of a key, and 128 channels: finite; times 1e30: infinite
+        kt[:, :, 200] = kt[:, :, 200] * 1e-30
+        kt[:, :, 201] = 1e30
+        qt[:, :, 78:] *= 1e-30
+        p = torch.full((1, 2, 200, (nkv + 3) // 4 * 4), 7.0, device="cuda")
+        mx.softmax_rows(qt, kt, out=p)
+        assert torch.all(torch.isnan(p[:, :, 77, :nkv])) and torch.all(p[:, :, :, nkv:] == 0)
+        assert torch.all(torch.isfinite(p[:, :, 78:]))
+        assert torch.all(torch.isfinite(good))
+        for mode, gamma in (("uos", 1.0), ("ocp_vanilla", 4.0), ("uos", 1.37)):
+            fused = mx.attention_rowsum_diag(qt, kt, mode, gamma).cpu().numpy()
+            two = mx.rowsum_diag(p, nkv, mode, gamma).cpu().numpy().reshape(fused.shape)
+            assert np.all(np.isnan(fused[:, :, 77, [1, 6]])) and np.all(fused[:, :, 77, [2, 3, 4, 5, 7]] == 0)
+            np.testing.assert_allclose(fused[:, :, 77], two[:, :, 77], rtol=1e-12)
+            _same_stats(fused[:, :, 78:], two[:, :, 78:], f"Nkv={nkv} {mode} gamma={gamma} beside a NaN row")
+
+
 def test_fused_diag_720p_sampled_rows(mx):
     """Whole 720p tensor diagnosed in one launch; sampled rows equal the
     diagnostic of the same rows materialized."""
