@@ -260,6 +260,32 @@ def test_rowsum_diag_unusual_entries(mx, mode, gamma, N):
         assert abs(change - 1.0) <= 1e-9, (label, got[2])
 
 
+@pytest.mark.parametrize("gamma", [1.0, 8.0, 1.37])
+@pytest.mark.parametrize("N", [100, 2051])
+def test_rowsum_diag_entropy_of_subnormals(mx, gamma, N):
+    """The entropy of rows whose terms are subnormal p, alone, beside a peak of 1
+    (whose own term is 0) and among normal values: relative 1e-6 (the fp32
+    logarithm), and half a unit in the last place of a product p log2 p below the
+    normal range, 2^-150 ln 2 per subnormal entry."""
+    ld = (N + 3) // 4 * 4
+    P = np.zeros((6, ld), np.float32)
+    P[0, :N] = np.float32(1e-40)
+    P[1, :N] = np.float32(2.0 ** -149)
+    P[2, :N] = np.resize(np.float32([0, 2.0 ** -126, 2.0 ** -127, 3e-39, 1e-44]), N)
+    P[3, N // 3:N] = np.resize(np.float32([0, 0, 0, 0, 7e-40]), N - N // 3)
+    P[3, 1] = 1.0
+    P[4, N - 1] = np.float32(5e-42)  # one entry, in the last block
+    P[5, :N] = _random_rows(3, 1, N, 2.0)[0]
+    P[5, 5:N:37] = np.float32(2e-39)
+    low = ((P[:, :N] > 0) & (P[:, :N] < 2.0 ** -126)).sum(axis=1)
+    for mode in MODES:
+        got = mx.rowsum_diag(torch.from_numpy(P).cuda(), N, mode, gamma).cpu().numpy()
+        ref = oracle.rowsum_diag(P, N, MODES[mode], gamma)
+        err = np.abs(got[:, 7] - ref[:, 7])
+        bound = 1e-6 * ref[:, 7] + low * 2.0 ** -150 * math.log(2)
+        assert np.all(ref[:, 7] > 0) and np.all(err <= bound), (mode, gamma, N, err / ref[:, 7], bound / ref[:, 7])
+
+
 def test_rows_without_a_finite_normalizer(mx):
     """Scores that overflow make a row of NaN: p past the end is 0 all the same,
     the statistics are those of such a row, and the other rows are not touched."""
