@@ -769,6 +769,26 @@ static void launch_attn_diag(const SoftmaxRowsArgs& a, int out, dim3 grid, hipSt
         attn_rows_kernel<kRowsDiagOcp, kGamma><<<grid, 256, 0, stream>>>(a);
 }
 
+// Whether m and L are formed apart from p (rows_norm_kernel, rows_write_kernel)
+// or in one launch (attn_rows_kernel, three workgroups per CU).  A CU holds one
+// workgroup of rows_norm_kernel (316 VGPRs), so beyond 256 row tiles it takes a
+// second round; with fewer, what the second launch and the second read of the
+// keys cost is repaid by p on the whole chip the sooner the fewer tiles there are
+// and the longer the rows.  Measured, one launch against two, us:
+//   tiles    keys 1300       1600       2048       4096        8192        32760
+//     40     58 |  54    68 |  57   81 |  61  157 |  87   310 |  145  1411 |  673
+//    120     60 |  59    70 |  62   82 |  65  162 | 139   354 |  254  1623 | 1134
+//    200     64 |  70    73 |  72   86 |  81  193 | 195   419 |  350  2005 | 1591
+//    256     67 |  77    75 |  77   90 |  90  216 | 209   445 |  410  2222 | 1888
+//    320     93 | 112   101 | 113  124 | 155  281 | 292   572 |  569  2775 | 2656
+//    400    102 | 141   109 | 145  137 | 192  289 | 355   625 |  670  (16384: 1274 | 1305)
+// and from 512 tiles on two launches are 10 to 50 % slower at every length.
+static bool apart(int64_t tiles, int Nkv) {
+    if (tiles <= 128) return Nkv >= 1280;
+    if (tiles <= 256) return Nkv >= 2048;
+    return tiles <= 320 && Nkv >= 8192;
+}
+
 hipError_t launch_attn_rows(const SoftmaxRowsArgs& args, int64_t BH, int out, hipStream_t stream) {
     SoftmaxRowsArgs a = args;
     a.qtiles = (a.rows + kRowsPerWg - 1) / kRowsPerWg;
@@ -783,9 +803,7 @@ hipError_t launch_attn_rows(const SoftmaxRowsArgs& args, int64_t BH, int out, hi
         }
         return hipGetLastError();
     }
-    // 768 workgroups (three per CU) fill the chip: with fewer row tiles each
-    // run of keys gets a workgroup of its own for p
-    if (a.runs < 2 || tiles >= 768) {
+    if (!apart(tiles, a.Nkv)) {
         attn_rows_kernel<kRowsStoreP, kGammaOne><<<dim3((unsigned)tiles), 256, 0, stream>>>(a);
         return hipGetLastError();
     }

@@ -184,7 +184,7 @@ def test_runs_of_keys_agree_between_the_paths(mx, nkv):
     qt = mx.bf16_from_bits(np.ascontiguousarray(q[:, :, :1024]))
     kt = mx.bf16_from_bits(np.ascontiguousarray(k[:, :, :nkv]))
     few = mx.softmax_rows(qt, kt, 900, 124)[..., :nkv]
-    if nkv == 1025:  # 768 row tiles: the undivided launch
+    if nkv == 2049:  # 768 row tiles: the undivided launch
         many = mx.softmax_rows(qt, kt)[..., :nkv]
         assert torch.equal(many[:, :, 900:], few)
         del many
@@ -196,6 +196,20 @@ def test_runs_of_keys_agree_between_the_paths(mx, nkv):
         _same_stats(fused, two, f"Nkv={nkv} {mode} gamma={gamma}")
     _softmax_check(mx, np.ascontiguousarray(q[:, :2, :1024]), np.ascontiguousarray(k[:, :2, :nkv]), 1000, 24,
                    f"Nkv={nkv}")
+
+
+@pytest.mark.parametrize("nkv", [1279, 1280, 1283, 2047, 2048, 2051, 4095, 8191, 8192])
+def test_softmax_rows_forms_agree(mx, nkv):
+    """P from one launch and from two (m and L apart from p) on both sides of the
+    rule's lines, in row tiles (128, 256, 320) and in keys (1280, 2048, 8192): bit
+    for bit the rows of a launch of 384 row tiles, which is one launch always."""
+    g = torch.Generator(device="cuda").manual_seed(nkv)
+    q, k = (torch.randn((1, 3, n, 128), generator=g, device="cuda").bfloat16() for n in (16384, nkv))
+    want = mx.softmax_rows(q, k)[..., :nkv]
+    for tiles in (1, 42, 43, 85, 86, 106, 107):  # per head: 3 .. 321 in all
+        rows = 128 * tiles - 5
+        got = mx.softmax_rows(q, k, 16384 - rows, rows)[..., :nkv]
+        assert torch.equal(got.view(torch.int32), want[:, :, 16384 - rows:].view(torch.int32)), (nkv, tiles)
 
 
 @pytest.mark.parametrize("mode", list(MODES))
