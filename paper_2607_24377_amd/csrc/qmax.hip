@@ -121,9 +121,14 @@ __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __re
     };
     uint4 next[2];
     fetch(r0, next);
-    for (int64_t base = r0; base < r1; base += 32) {  // same trip count in every lane
+    // A wave without rows leaves the loop, and lanes without one add nothing: they
+    // would add zeros, but all to the same bins, one atomic after another (5000
+    // heads of 33 rows 40.8 us so, 28.9 without).
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int64_t base = r0; base + 8 * wave < r1; base += 32) {  // same trip count in a wave's lanes
         const uint4 v0 = next[0], v1 = next[1];
         fetch(base + 32, next);
+        const bool ok = base + (threadIdx.x >> 3) < r1;
         uint32_t m2 = max_halves(max_halves(0u, v0), v1);
         m2 = max_halves(m2, swap1(m2));
         const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
@@ -141,9 +146,9 @@ __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __re
         if (F == 0) {
             double sm = lane_sse(em);
             sm += swap1(sm);
-            if (threadIdx.x & 1) atomicAdd(&hist[256], ldexp(sm, 2 * em));
+            if (ok && (threadIdx.x & 1)) atomicAdd(&hist[256], ldexp(sm, 2 * em));
         }
-        // rows past the end hold zeros, which add nothing
+        if (!ok) continue;
         if (threadIdx.x & 1)
             atomicAdd(&hist[128 + F], ldexp(s0, 2 * e0));
         else
@@ -157,7 +162,12 @@ __global__ __launch_bounds__(256) void sse_hist_headdim_kernel(const uint4* __re
 // Blocks along the tokens (32 tokens of one channel; the last block padded
 // with +0, which adds no error): a workgroup stages 128 tokens x 128 channels
 // in LDS, wave w takes token block w of the group and each lane a pair of
-// channels.  A workgroup covers token groups [c * groups_per_chunk, ...).
+// channels.  A workgroup covers token groups [c * groups_per_chunk, ...); kOne: one
+// of at most 64 tokens, so that no registers are held for the next group's loads
+// (110 instead of 142, four workgroups per CU instead of three: 20000 heads of one
+// token 142 -> 115 us, 4000 of 17 34 -> 29; at 100 tokens 26.8 against 25.9 with
+// all loads ahead).
+template <bool kOne>
 __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __restrict__ x,
                                                               double* __restrict__ partial, int N,
                                                               int groups, int groups_per_chunk,
@@ -173,27 +183,27 @@ __global__ __launch_bounds__(256) void sse_hist_tokens_kernel(const uint4* __res
     const int w = tid >> 6, cp = tid & 63;
     // the next group's loads are in flight while a group is worked on
     uint4 buf[8];
-    auto fetch = [&](int g) {
-        const int tok0 = g * kTokGroup;
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const int ch = tid + 256 * k;
-            const int tok = ch >> 4, part = ch & 15;
-            buf[k] = g < g1 && tok0 + tok < N ? src[(int64_t)(tok0 + tok) * 16 + part] : make_uint4(0, 0, 0, 0);
-        }
+    auto chunk = [&](int g, int k) {
+        const int ch = tid + 256 * k;
+        const int tok = g * kTokGroup + (ch >> 4), part = ch & 15;
+        return g < g1 && tok < N ? src[(int64_t)tok * 16 + part] : make_uint4(0, 0, 0, 0);
     };
-    fetch(g0);
+    auto fetch = [&](int g) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) buf[k] = chunk(g, k);
+    };
+    if constexpr (!kOne) fetch(g0);
     for (int g = g0; g < g1; g++) {
         const int tok0 = g * kTokGroup;
-        __syncthreads();  // previous group's reads (and the zeroed histogram)
+        if constexpr (!kOne) __syncthreads();  // previous group's reads
 #pragma unroll
         for (int k = 0; k < 8; k++) {
             const int ch = tid + 256 * k;
             const int tok = ch >> 4, part = ch & 15;
-            *reinterpret_cast<uint4*>(&tile[tok * 64 + part * 4]) = buf[k];
+            *reinterpret_cast<uint4*>(&tile[tok * 64 + part * 4]) = kOne ? chunk(g, k) : buf[k];
         }
         __syncthreads();
-        fetch(g + 1);
+        if constexpr (!kOne) fetch(g + 1);
         if (tok0 + 32 * w >= N) continue;  // block entirely past the sequence end
 
         uint32_t col[32];
@@ -302,8 +312,8 @@ hipError_t launch_qmax_sse(const void* x, int axis, const double* qs, int nq, do
                                                           sp.chunks);
     } else {
         const int groups = (int)((N + kTokGroup - 1) / kTokGroup);
-        sse_hist_tokens_kernel<<<grid, 256, 0, stream>>>((const uint4*)x, partial, (int)N, groups,
-                                                         (int)sp.per_chunk, sp.chunks);
+        const auto kernel = N <= 64 ? sse_hist_tokens_kernel<true> : sse_hist_tokens_kernel<false>;
+        kernel<<<grid, 256, 0, stream>>>((const uint4*)x, partial, (int)N, groups, (int)sp.per_chunk, sp.chunks);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

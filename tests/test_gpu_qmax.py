@@ -203,3 +203,20 @@ def test_workload_optimum_distribution(mx):
         tot = sum(cnt.values())
         top = ", ".join(f"{q:.2f}: {100.0 * c / tot:.1f}%" for q, c in cnt.most_common(4))
         log(f"[qmax optimum] {wname} {t} ({tot} heads): {top}")
+
+
+@pytest.mark.parametrize("N", [1, 17, 33, 64, 65, 128, 129, 300])
+def test_sse_of_many_short_heads(mx, N):
+    """More heads than the chip has room for, so one workgroup per head, whose last
+    step is mostly past the end: each head's sums equal those of the head alone,
+    which is divided differently, up to the order of the fp64 additions."""
+    heads, qs = 2100, [4.0, 6.0, 7.25, 8.0]
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randn((1, heads, N, 128), generator=g, device="cuda").bfloat16()
+    x[:, 5] = 0.5  # block maxima that are powers of two, in rows up to the last
+    x[:, 7] = 0.0
+    for axis in (mx.AXIS_HEAD_DIM, mx.AXIS_TOKENS):
+        got = mx.qmax_sse(x, axis, qs)
+        for h in (0, 5, 7, 1000, heads - 1):
+            alone = mx.qmax_sse(x[:, h:h + 1].contiguous(), axis, qs)[0]
+            torch.testing.assert_close(got[h], alone, rtol=1e-12, atol=0.0)
