@@ -496,7 +496,6 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     a.N = (int)Nkv;
     a.Nq = (int)Nq;
     a.ntiles = (int)ntiles;
-    a.qtiles = (int)((Nq + 127) / 128);
     int st = MXATTN_OK;
     if (hipError_t e = mxattn::launch_prepare_operands(a, rule_of(mode), !q_fused, s)) {
         set_error("quantize launch", e);

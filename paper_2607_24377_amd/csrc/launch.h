@@ -36,8 +36,8 @@ struct PrepareArgs {
     uint8_t* vc;             // [BH, ntiles, 128, 64]
     uint8_t* sc;             // [BH, ntiles, 1024]
     int64_t BH;
-    int N, Nq, ntiles, qtiles;  // tiles of 128 tokens
-    int64_t first;              // set by the launcher: first workgroup of a launch
+    int N, Nq, ntiles;  // tiles of 128 tokens of a head
+    int64_t first;      // set by the launcher: first workgroup of a launch
 };
 hipError_t launch_prepare_operands(const PrepareArgs& a, int rule, bool rotated, hipStream_t stream);
 

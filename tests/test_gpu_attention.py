@@ -210,6 +210,22 @@ def test_forward_operands_equal_the_public_ones(mx, Nq, Nkv):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (Nq, Nkv, mode)
 
 
+@pytest.mark.parametrize("Nq,Nkv", [(1, 1), (7, 33), (16, 16), (50, 64), (3, 65), (31, 96), (5, 97), (2, 127)])
+def test_many_short_heads(mx, Nq, Nkv):
+    """300 heads shorter than a tile: the rotated mode's Q is prepared in tiles that
+    run on over the heads, K and V in one tile per head; as above, the output
+    equals the one on the standalone quantizers' codes bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(100 * Nq + Nkv)
+    q, k, v = (torch.randn((2, 150, n, 128), generator=g, device="cuda").bfloat16() for n in (Nq, Nkv, Nkv))
+    for mode in MODES + ["uos_pnq_rot"]:
+        a = mx.cross_forward(q, k, v, mode)
+        qc, qs = mx.quantize(q, mx.AXIS_HEAD_DIM, mode)
+        kc, ks = mx.quantize(k, mx.AXIS_HEAD_DIM, mode)
+        vc, vs = mx.quantize(v, mx.AXIS_TOKENS, mode)
+        b = mx.cross_attend(qc, qs, kc, ks, vc, vs, Nq, Nkv, mode)
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (Nq, Nkv, mode)
+
+
 def test_workspace_across_streams_and_threads(mx):
     """Calls on the null stream share one kept block of workspace, those on
     other streams and of a second thread at the same time do not: every output
