@@ -202,7 +202,8 @@ int mxattn_attention_rowsum_diag(const void* q, const void* k, int64_t B, int64_
  * MXATTN_UOS_PNQ_ROT only; non-causal, no mask besides the sequence end).
  * Quantizes K along d and V along N into stream-ordered workspace (from
  * the library's pool on `stream`, see mxattn_release_workspace; about 0.53
- * bytes per element of each of K and V; calls with few queries over many keys
+ * bytes per element of each of K and V, the scales in whole tiles of 128 keys
+ * and V too where there are more than 96; calls with few queries over many keys
  * take up to 34 MiB more, for partial results of runs of the keys), then runs
  * the fused kernel, which quantizes Q along d in
  * its prologue with codes bit-identical to mxattn_quantize's; in

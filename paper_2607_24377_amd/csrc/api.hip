@@ -259,9 +259,9 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
     a.kc = kc;
     a.vc = vc;
     const int ntiles = (int)((Nkv + mxattn::kKvTile - 1) / mxattn::kKvTile);
-    a.vrow = v_tiled ? 64 : (int)((Nkv + 31) / 32) * 16;
-    a.vtile = v_tiled ? 8192 : 64;
-    a.vhead = v_tiled ? ntiles * 8192 : 128 * a.vrow;
+    a.vrow = v_tiled ? mxattn::v_tile_row_bytes(Nkv) : (int)((Nkv + 31) / 32) * 16;
+    a.vtile = v_tiled ? 128 * a.vrow : 64;
+    a.vhead = v_tiled ? ntiles * a.vtile : 128 * a.vrow;
     a.sc = sc;
     a.out = static_cast<uint16_t*>(out);
     a.N = (int)Nkv;
@@ -464,7 +464,7 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     const size_t q_scales = q_fused ? 0 : mxattn_scales_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nq, d);
     const size_t k_codes = mxattn_codes_bytes(MXATTN_AXIS_HEAD_DIM, B, H, Nkv, d);
     const int64_t ntiles = (Nkv + mxattn::kKvTile - 1) / mxattn::kKvTile;
-    const size_t v_codes = (size_t)(B * H * ntiles * 8192);
+    const size_t v_codes = (size_t)(B * H * ntiles * 128 * mxattn::v_tile_row_bytes(Nkv));
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t tiled = (size_t)mxattn::tile_scales_bytes(B * H, Nkv);
     const size_t split = mxattn::split_bytes(B * H, Nq, mxattn::key_splits(B * H, Nq, Nkv));
@@ -496,6 +496,7 @@ int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out,
     a.N = (int)Nkv;
     a.Nq = (int)Nq;
     a.ntiles = (int)ntiles;
+    a.vrow = mxattn::v_tile_row_bytes(Nkv);
     int st = MXATTN_OK;
     if (hipError_t e = mxattn::launch_prepare_operands(a, rule_of(mode), !q_fused, s)) {
         set_error("quantize launch", e);

@@ -33,12 +33,17 @@ struct PrepareArgs {
     const uint4 *q, *k, *v;  // bf16 [BH, Nq or N, 128]
     uint8_t *qc, *qs;        // [BH, Nq, 64], [BH, Nq, 4]
     uint8_t* kc;             // [BH, N, 64]
-    uint8_t* vc;             // [BH, ntiles, 128, 64]
+    uint8_t* vc;             // [BH, ntiles, 128, vrow]
     uint8_t* sc;             // [BH, ntiles, 1024]
     int64_t BH;
     int N, Nq, ntiles;  // tiles of 128 tokens of a head
+    int vrow;           // v_tile_row_bytes(N)
     int64_t first;      // set by the launcher: first workgroup of a launch
 };
+// Bytes of a channel in a tile of V^ codes stored tile by tile: those of the tile's
+// four blocks, or of the blocks that there are in a head shorter than a tile (one
+// block: 2 KiB per head instead of 8).
+inline int v_tile_row_bytes(int64_t N) { return N > 96 ? 64 : (int)((N + 31) / 32) * 16; }
 hipError_t launch_prepare_operands(const PrepareArgs& a, int rule, bool rotated, hipStream_t stream);
 
 // Per-head squared-error sweep over boundaries (qmax.hip).  The histogram
@@ -59,7 +64,7 @@ struct AttnArgs {
     uint16_t* out;      // [BH, Nq, 128] bf16
     int N;              // keys / values per head
     int Nq;             // queries per head (Q^ codes/scales and out are [BH, Nq, ...])
-    int vrow, vtile, vhead;  // bytes; [BH, 128, nb * 16] or [BH, ntiles, 128, 64]
+    int vrow, vtile, vhead;  // bytes; [BH, 128, nb * 16] or [BH, ntiles, 128, v_tile_row_bytes]
     int qtiles;
     int total_tiles;    // workgroups that do work
     int per_xcd;

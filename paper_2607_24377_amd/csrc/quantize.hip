@@ -333,7 +333,8 @@ __global__ __launch_bounds__(kVqThreads) void quantize_tokens_kernel(const uint4
 // the tokens and, in the rotated mode, Q, in the layouts the attention kernel
 // reads.  A workgroup takes one 128-token tile of one tensor and head (32 KiB
 // of bf16, loaded at once: 128 bytes in flight per thread):
-//   V  codes as [head][tile][channel][64 B] (8 KiB per workgroup, contiguous;
+//   V  codes as [head][tile][channel][64 B] (8 KiB per workgroup, contiguous, less
+//      in a head shorter than a tile;
 //      the public layout's 128 channel rows lie 38 KB apart at 720p), staged
 //      through LDS as quantize_tokens_kernel does it, one lane per channel
 //      pair and block;
@@ -400,9 +401,11 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_operands_kernel(PrepareA
         uint4 c0, c1;
         uint32_t s0, s1;
         quantize_token_pair<kRule>(col, Boundary{}, c0, c1, s0, s1);
-        uint8_t* dst = a.vc + (bh * a.ntiles + t) * 8192 + cp * 128 + b * 16;
-        *reinterpret_cast<uint4*>(dst) = c0;
-        *reinterpret_cast<uint4*>(dst + 64) = c1;
+        if (16 * b < a.vrow) {
+            uint8_t* dst = a.vc + ((bh * a.ntiles + t) * 128 + 2 * cp) * a.vrow + b * 16;
+            *reinterpret_cast<uint4*>(dst) = c0;
+            *reinterpret_cast<uint4*>(dst + a.vrow) = c1;
+        }
         // channel d: lane (d & 31) + 32 (b & 1), byte 2 (d >> 5) + (b >> 1)
         const int d = 2 * cp;
         uint8_t* sc = a.sc + (bh * a.ntiles + t) * 1024 + 512 + ((d & 31) + 32 * (b & 1)) * 8 + 2 * (d >> 5) + (b >> 1);

@@ -226,6 +226,22 @@ def test_many_short_heads(mx, Nq, Nkv):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (Nq, Nkv, mode)
 
 
+def test_workspace_of_short_heads(mx):
+    """65536 heads of one key: K^ and V^ of one block and 1 KiB of scales per head
+    (206 MB in all), not a whole tile of V^ codes (8 KiB instead of 2)."""
+    x = torch.ones((1, 65536, 1, 128), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(x)
+    torch.cuda.synchronize()
+    mx.release_workspace()
+    free = torch.cuda.mem_get_info()[0]
+    mx.forward(x, x, x, "uos", out=out)
+    torch.cuda.synchronize()
+    taken = free - torch.cuda.mem_get_info()[0]
+    mx.release_workspace()
+    assert torch.all(out == 1)
+    assert taken <= 65536 * (64 + 128 * 16 + 1024) + (32 << 20), taken  # and the pool's granularity
+
+
 def test_workspace_across_streams_and_threads(mx):
     """Calls on the null stream share one kept block of workspace, those on
     other streams and of a second thread at the same time do not: every output
