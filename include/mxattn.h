@@ -204,7 +204,8 @@ int mxattn_attention_rowsum_diag(const void* q, const void* k, int64_t B, int64_
  * the library's pool on `stream`, see mxattn_release_workspace; about 0.53
  * bytes per element of each of K and V, the scales in whole tiles of 128 keys
  * and V too where there are more than 96; calls with few queries over many keys
- * take up to 34 MiB more, for partial results of runs of the keys), then runs
+ * take up to 34 MiB more, for partial results of runs of the keys, see
+ * mxattn_cross_forward), then runs
  * the fused kernel, which quantizes Q along d in
  * its prologue with codes bit-identical to mxattn_quantize's; in
  * MXATTN_UOS_PNQ_ROT, Q is rotated and quantized into the workspace first
@@ -237,7 +238,15 @@ int mxattn_attend(const uint8_t* q_codes, const uint8_t* q_scales, const uint8_t
  * k and v are [B, H, Nkv, d]; the quantized variants take Q^ blocked along d
  * with Nq rows, K^ blocked along d with Nkv rows and V^ blocked along Nkv.
  * Otherwise as mxattn_forward / mxattn_attend, which are these calls with
- * Nq = Nkv = N; the key limit N <= 2^24 applies to Nkv. */
+ * Nq = Nkv = N; the key limit N <= 2^24 applies to Nkv.
+ *
+ * Calls whose query tiles (128 queries of one head) leave most of the chip idle
+ * divide the keys of a head into runs; whether and into how many follows from
+ * B * H, Nq and Nkv.  The running maximum, P~ and P^ are those of the undivided
+ * sequence, but O~ and l are sums of fp32 partial sums: an output element may
+ * differ by one bf16 unit in the last place (about one in 10 000 does) between
+ * calls that divide the same head differently, as a call of all heads and one
+ * of a few of them may.  Equal shapes give equal bits. */
 int mxattn_cross_forward(const void* q, const void* k, const void* v, void* out, int64_t B,
                          int64_t H, int64_t Nq, int64_t Nkv, int64_t d, int mode, void* stream);
 int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const uint8_t* k_codes,

@@ -604,7 +604,7 @@ struct SplitRange {
     int first, tiles;
 };
 __device__ __forceinline__ SplitRange split_range(const AttnArgs& a, int s) {
-    const int nt = (a.N + 127) / 128;  // nt * nsplit < 2^26
+    const int nt = (a.N + 127) / 128;  // nt * nsplit <= 2^26
     const int first = nt * s / a.nsplit;
     return {first, nt * (s + 1) / a.nsplit - first};
 }
