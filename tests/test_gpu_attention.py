@@ -282,6 +282,62 @@ def test_workspace_across_streams_and_threads(mx):
     assert not bad, bad
 
 
+def test_kept_block_is_reused_without_waiting(mx):
+    """Calls enqueued one after another on the null stream, with no synchronization
+    until the end, overwrite the kept block while earlier ones still run: sizes that
+    grow it on the way, quantized operands and the sweep's partial sums beside the
+    forward's, and calls of two threads and of another stream at the same time."""
+    import threading
+
+    shapes = [(1, 2, 300), (2, 3, 1000), (1, 1, 40), (1, 8, 4000), (1, 4, 2000), (1, 20, 3000)]
+    data = []
+    for i, (B, H, N) in enumerate(shapes):
+        g = torch.Generator(device="cuda").manual_seed(50 + i)
+        t = [torch.randn((B, H, N, 128), generator=g, device="cuda").bfloat16() for _ in range(3)]
+        ops = [x for n, ax in zip(t, (mx.AXIS_HEAD_DIM, mx.AXIS_HEAD_DIM, mx.AXIS_TOKENS)) for x in mx.quantize(n, ax, "uos_pnq")]
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):  # pool memory of the call's own
+            want = mx.forward(*t, "uos_pnq")
+            sse = mx.qmax_sse(t[0], mx.AXIS_TOKENS, [6.0, 7.25])
+        side.synchronize()
+        data.append((t, ops, want, sse))
+    mx.release_workspace()
+    results = []
+
+    def work(stream, order, outs):
+        with torch.cuda.stream(stream):
+            for n, i in enumerate(order):
+                t, ops, want, sse = data[i]
+                if n % 3 == 0:
+                    mx.forward(*t, "uos_pnq", out=outs[n])
+                elif n % 3 == 1:
+                    mx.attend(*ops, t[0].shape[2], "uos_pnq", out=outs[n])
+                else:
+                    mx.qmax_sse(t[0], mx.AXIS_TOKENS, [6.0, 7.25], out=outs[n])
+
+    rng = np.random.default_rng(8)
+    threads = []
+    null, side = torch.cuda.default_stream(), torch.cuda.Stream()
+    for stream in (null, null, side):
+        order = [2, 0, 0, 2, 4, 1] + [int(i) for i in rng.integers(0, len(shapes), 54)]
+        outs = [torch.empty_like(data[i][3] if n % 3 == 2 else data[i][2]) for n, i in enumerate(order)]
+        results.append((order, outs))
+        threads.append(threading.Thread(target=work, args=(stream, order, outs)))
+    torch.cuda.synchronize()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for order, outs in results:
+        for n, (i, out) in enumerate(zip(order, outs)):
+            if n % 3 == 2:
+                torch.testing.assert_close(out, data[i][3], rtol=1e-12, atol=0.0)
+            else:
+                assert torch.equal(out.view(torch.int16), data[i][2].view(torch.int16)), (n, shapes[i])
+
+
 def test_release_does_not_wait_for_the_null_stream(mx):
     """A release while calls are under way returns at once; the block that they
     use is given back by a release after they have completed."""
