@@ -268,11 +268,14 @@ static int launch_attend(const void* qraw, const uint8_t* qc, const uint8_t* qs,
     a.Nq = (int)Nq;
     a.qtiles = (int)((Nq + mxattn::kQueryTile - 1) / mxattn::kQueryTile);
     // one query tile per workgroup; with K^/V^ resident in LDS, chunks of at
-    // most 16 query tiles, as many as fill whole rounds of the 512 workgroups
-    // resident at once (two per CU), split evenly by the kernel
+    // most 16 query tiles, as many as fill whole rounds of the workgroups
+    // resident at once, split evenly by the kernel.  Those are 512, two per CU;
+    // of the one-tile kernels on quantized Q (152 VGPRs, 26 KB of LDS) three fit:
+    // attend, 40 heads x 32760 queries x 128 keys 108.2 us in rounds of 512, 97.3
+    // in rounds of 768; on bf16 Q (164 to 179 VGPRs) the same call 144 and 158
     int64_t nchunks = a.qtiles;
     if (Nkv <= mxattn::kResidentKeys) {
-        const int64_t slots = 512, bh = B * H;
+        const int64_t slots = ntiles == 1 && !qraw ? 768 : 512, bh = B * H;
         const int64_t min_chunks = (a.qtiles + 15) / 16;
         const int64_t rounds = (bh * min_chunks + slots - 1) / slots;
         const int64_t k = rounds * slots / bh;

@@ -112,6 +112,17 @@ def test_resident_staged_stores_several_query_tiles(mx):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("H,Nq,Nkv", [(16, 16500, 100), (40, 3000, 128), (770, 130, 20)])
+def test_resident_one_key_tile(mx, H, Nq, Nkv):
+    # one key tile: query tiles split for 512 workgroups at once on bf16 Q, for 768
+    # on quantized Q (the forward and attend of the check), also where that is
+    # several tiles per workgroup or more workgroups than a round holds
+    w = inputs.Workload(74, f"cross_{H}x{Nq}x{Nkv}", 1, H, Nq, 128, "cross", Nkv=Nkv)
+    for mode in MODES:
+        _check(mx, w, mode, [0, H - 1], 40, w.name)
+    torch.cuda.empty_cache()
+
+
 # few query tiles over many keys: the keys are divided into runs that several
 # workgroups take (the last case: one tile less than the shortest divided one)
 @pytest.mark.parametrize("B,H,Nq,Nkv", [(1, 1, 130, 3073), (2, 2, 37, 8951), (1, 3, 300, 6400),
