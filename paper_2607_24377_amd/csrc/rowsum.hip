@@ -120,19 +120,25 @@ __device__ __forceinline__ v16f scores_t(const bf16x8* qb, const uint8_t* lds, i
 // otherwise 64 c + 32 j + 8 (i >> 2) + 4 h + (i & 3).
 typedef v16f TileScores[2][2];
 
-// -inf past the end of the sequence.
+// -inf past the end of the sequence: per score the sign of (last - its key)
+// selects the bits of -inf, so that the compares are not hoisted and held as 64
+// condition masks in scalar registers, which spilled (P of 26 rows over 7 keys 8.3
+// us with them, 7.0 so).
 template <bool kBlocks>
 __device__ __forceinline__ void mask_tail(int t, int Nkv, int h, TileScores& sv) {
     if ((t + 1) * kKeyTile > Nkv) {
-        const int valid = Nkv - t * kKeyTile - (kBlocks ? 32 : 4) * h;
+        const int last = Nkv - t * kKeyTile - (kBlocks ? 32 : 4) * h - 1;
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
-                for (int i = 0; i < 16; i++)
-                    if (64 * c + (kBlocks ? 16 * j + i : 32 * j + 8 * (i >> 2) + (i & 3)) >= valid)
-                        sv[c][j][i] = -INFINITY;
+                for (int i = 0; i < 16; i++) {
+                    const int past = (last - (64 * c + (kBlocks ? 16 * j + i : 32 * j + 8 * (i >> 2) + (i & 3)))) >> 31;
+                    const float s = sv[c][j][i];  // (a bit cast of a vector's element takes element 0)
+                    const int b = __builtin_bit_cast(int, s);
+                    sv[c][j][i] = __builtin_bit_cast(float, (past & (int)0xFF800000u) | (~past & b));
+                }
     }
 }
 
@@ -484,6 +490,7 @@ __device__ __forceinline__ void emit_tile(const SoftmaxRowsArgs& a, const RowPla
         for (int c = 0; c < 2; c++)
 #pragma unroll
             for (int pass = 0; pass < 2; pass++) {
+                if (row0 + 16 * pass >= a.rows || t * kKeyTile + 64 * c >= a.Nkv) continue;  // nothing to store
                 if ((w.col >> 4) == pass) {
                     const int row = w.col & 15;
 #pragma unroll
