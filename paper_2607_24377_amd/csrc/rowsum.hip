@@ -704,7 +704,8 @@ __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
         n1 = src[nb / 4 + 1];
         block(p);
     }
-    if (whole < a.N) {  // the rest of the row, zeros past its end
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (whole + 512 * wave < a.N) {  // the rest of the row, zeros past its end, in the waves that it reaches
         const int64_t j = whole + 8 * threadIdx.x;
         float p[8];
 #pragma unroll
@@ -718,7 +719,6 @@ __global__ __launch_bounds__(256) void rowsum_diag_kernel(RowsumDiagArgs a) {
         }
         block(p);
     }
-    const int wave = threadIdx.x >> 6;
     auto reduce = [&](bool flag) {
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
