@@ -32,18 +32,19 @@
 // two, so another association of L (4e-5 at 32760 keys, where the chain rounds
 // small terms away) moves whole entries of P^, and a row by up to 0.3.  L is
 // therefore not divided over workgroups.  p given m and L is: a launch with few
-// row tiles, which would leave most of the chip idle, forms m and L in one
-// workgroup per row tile (rows_norm_kernel) and p in one per 8 key tiles
+// row tiles of long rows, which would leave most of the chip idle, forms m and L in
+// one workgroup per row tile (rows_norm_kernel) and p in one per 8 key tiles
 // (rows_write_kernel).  Both ways form m, L and p from the same operations in
 // the same order, bit for bit.
 //
-// What bounds them (one MI355X): the fused diagnostic vector issue (about 30
-// vector instructions per entry over the two passes: 40 heads x 4096^2 entries
-// in 0.75 ms; with every class summed per entry in fp64 behind compares and
-// selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries the chain
-// of L in 40 workgroups, one wave per SIMD (0.41 ms), then HBM (P written, 0.25
-// ms; both passes in one workgroup per row tile 2.9 ms), and their diagnostic
-// again vector issue (0.20 ms = 3.3 TB/s of P; before 0.24 ms).
+// What bounds them (one MI355X): the fused diagnostic vector issue (91 % of the
+// cycles, 33 vector instructions per entry over the two passes: 40 heads x 4096^2
+// entries in 0.73 ms; with every class summed per entry in fp64 behind compares and
+// selects 2.55 ms); the materialized rows of 40 x 128 x 32760 entries the
+// normalizer in 40 workgroups, one wave per SIMD (0.39 ms, see rows_norm_kernel),
+// then the stores of P (0.24 ms, 4.2 TB/s with the keys read; both passes in one
+// workgroup per row tile 1.35 ms), and their diagnostic vector issue and its own
+// chains (0.19 ms = 3.4 TB/s of P, vector issue in 67 % of the cycles).
 #include <cmath>
 
 #include "device_common.h"
@@ -578,10 +579,13 @@ __global__ __launch_bounds__(256, 3) void attn_rows_kernel(SoftmaxRowsArgs a) {
 // workgroup of rows_write_kernel reads those of its own run before it overwrites
 // them, so no other workspace is needed.
 //
-// One wave per SIMD: rows_norm_kernel scores tile t + 1 (a product after every
-// two entries) while the chain of tile t is added, with two tiles in LDS and
-// the next in flight.  40 heads x 128 rows x 32760 keys 413 us; scoring each tile
-// before its chain 475 us.
+// One wave per SIMD: rows_norm_kernel keeps two tiles in LDS and the next in
+// flight.  40 heads x 128 rows x 32760 keys 390 us; with one tile in LDS 475 us.
+// The loop below issues a product of tile t + 1 after every two entries of tile t,
+// but the compiler moves the exponentials and additions behind the branch of the
+// ragged tile, so a tile's 32 products (1030 cycles), 65 exponentials and 64
+// additions still follow one another: 3780 cycles per tile, 1890 of them vector
+// issue.
 __global__ __launch_bounds__(256) void rows_norm_kernel(SoftmaxRowsArgs a) {
     // (two arrays: reads of one do not wait for copies into the other)
     __shared__ __attribute__((aligned(16))) uint8_t lds0[kKeyTile * 256];
@@ -779,21 +783,23 @@ static void launch_attn_diag(const SoftmaxRowsArgs& a, int out, dim3 grid, hipSt
 // Whether m and L are formed apart from p (rows_norm_kernel, rows_write_kernel)
 // or in one launch (attn_rows_kernel, three workgroups per CU).  A CU holds one
 // workgroup of rows_norm_kernel (316 VGPRs), so beyond 256 row tiles it takes a
-// second round; with fewer, what the second launch and the second read of the
-// keys cost is repaid by p on the whole chip the sooner the fewer tiles there are
-// and the longer the rows.  Measured, one launch against two, us:
-//   tiles    keys 1300       1600       2048       4096        8192        32760
-//     40     58 |  54    68 |  57   81 |  61  157 |  87   310 |  145  1411 |  673
-//    120     60 |  59    70 |  62   82 |  65  162 | 139   354 |  254  1623 | 1134
-//    200     64 |  70    73 |  72   86 |  81  193 | 195   419 |  350  2005 | 1591
-//    256     67 |  77    75 |  77   90 |  90  216 | 209   445 |  410  2222 | 1888
-//    320     93 | 112   101 | 113  124 | 155  281 | 292   572 |  569  2775 | 2656
-//    400    102 | 141   109 | 145  137 | 192  289 | 355   625 |  670  (16384: 1274 | 1305)
+// second round and two launches never gain; with fewer, what the second launch and
+// the second read of the keys cost is repaid by p on the whole chip the sooner the
+// fewer tiles there are and the longer the rows.  Measured, one launch against
+// two, us:
+//   tiles   keys 1300      1600       2048       3000       4096       8192       32760
+//     40     54 |  52   63 |  54   77 |  58  114 |  71  149 |  83  292 | 139  1348 |  660
+//    128     57 |  56   66 |  59   79 |  63  116 |  95  156 | 139  338 | 254  1590 | 1146
+//    160     58 |  63   67 |  66   80 |  74  119 | 107  167 | 157  378 | 294  1759 | 1352
+//    200     60 |  68   68 |  68   82 |  80  144 | 136  185 | 191  410 | 348  1961 | 1582
+//    256     65 |  76   72 |  73   90 |  91  167 | 181  211 | 204  436 | 407  2180 | 1872
+//    280     83 | 109   88 | 108  114 | 148  200 | 238  237 | 268  491 | 514  2417 | 2388
+//    400     97 | 133  106 | 139  136 | 190  253 | 301  279 | 350  577 | 662  2867 | 3098
 // and from 512 tiles on two launches are 10 to 50 % slower at every length.
 static bool apart(int64_t tiles, int Nkv) {
     if (tiles <= 128) return Nkv >= 1280;
-    if (tiles <= 256) return Nkv >= 2048;
-    return tiles <= 320 && Nkv >= 8192;
+    if (tiles <= 192) return Nkv >= 2048;
+    return tiles <= 256 && Nkv >= 4096;
 }
 
 hipError_t launch_attn_rows(const SoftmaxRowsArgs& args, int64_t BH, int out, hipStream_t stream) {
