@@ -262,9 +262,9 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
  * buffer beyond the inputs and `out`, the K^ and V^ scales rearranged into
  * the kernel's operand order (1 KiB per (batch, head) and 128-key tile), is
  * a static device array of MXATTN_NOALLOC_SCRATCH_BYTES, followed by 34 MiB for
- * the partial results of calls with few queries over many keys, that each
- * device the library runs on holds until the process ends.  Limit: B * H * ceil(Nkv /
- * 128) <= 32768 (e.g. H = 40 heads of up to 104 832 keys), else
+ * the partial results of calls with few queries over many keys, which a device
+ * holds from the first such call on it until the process ends.  Limit: B * H *
+ * ceil(Nkv / 128) <= 32768 (e.g. H = 40 heads of up to 104 832 keys), else
  * MXATTN_ERR_SCRATCH with a message in mxattn_last_error and nothing
  * launched.  The array is fully rewritten by every call before it is read,
  * but all calls on one device share it: calls that overlap in time on one

@@ -368,8 +368,10 @@ int mxattn_cross_attend(const uint8_t* q_codes, const uint8_t* q_scales, const u
 // mxattn_cross_attend_noalloc keeps its one buffer beyond the inputs and the
 // output, the K^/V^ scales rearranged into MFMA operand order (1 KiB per
 // (batch, head) and 128-key tile), in this static device array instead of
-// allocated workspace, with the partial results of divided keys behind it.  Each device the library runs on holds its own copy
-// until the process ends.  On the host, `scratch` is only a stand-in symbol,
+// allocated workspace, with the partial results of divided keys behind it.  A
+// device holds its own copy from the first such call on it until the process ends
+// (the runtime loads this file's device code, which is nothing else, when its
+// address is first asked for).  On the host, `scratch` is only a stand-in symbol,
 // never a device address: the device address comes from hipGetSymbolAddress,
 // taken once per device with that device current, and only that address is
 // passed to kernels.  Every call on a device shares the device's array, so
